@@ -84,7 +84,7 @@ GmiPlan plan_gmi(const mdgmi_format* f, int64_t n, int n_snr, int path, int mode
     p.path = path;
     const int per_launch = std::min(n_snr, kMaxSnrPerLaunch);
     if (path == MDGMI_PATH_F64) {
-        p.cfg = f64_cfg(f, n);
+        p.cfg = f64_cfg(f, n, n_snr, mode);
         p.image_bytes = 0;
     } else if (path == MDGMI_PATH_F32_DIRECT) {
         p.cfg = direct_cfg(f, n);
@@ -95,6 +95,10 @@ GmiPlan plan_gmi(const mdgmi_format* f, int64_t n, int n_snr, int path, int mode
         p.image_bytes = mfma_image_bytes(f, per_launch, split);
     }
     int64_t blocks = (int64_t)n_snr * p.cfg.blocks_per_snr;
+    // FP64 launches take fewer blocks per point the more points share them,
+    // and not always more for more samples: room for any call over at most
+    // these samples and points
+    if (path == MDGMI_PATH_F64) blocks = std::max(blocks, (int64_t)n_snr * f64_blocks_bound(n));
     // MFMA launch shapes follow the tuning table, per sample-count regime:
     // room for whichever shape a call over these samples (or a subset of
     // the SNR points) may take

@@ -87,7 +87,8 @@ struct LaunchCfg {
 hipError_t launch_generate(const mdgmi_format* f, uint64_t seed, const double* sigma2, int n_snr,
                            int64_t n, int snr_slot0, void* y, uint32_t* tx, bool f64, hipStream_t st);
 
-LaunchCfg f64_cfg(const mdgmi_format* f, int64_t n);
+LaunchCfg f64_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode);
+int64_t f64_blocks_bound(int64_t n);  // at least the blocks per point of n or fewer samples, any number of points
 hipError_t launch_f64(const mdgmi_format* f, const double* y, const uint32_t* tx, int64_t n,
                       const SnrArgs& sa, int mode, double* llr, double* part, LaunchCfg cfg,
                       hipStream_t st);

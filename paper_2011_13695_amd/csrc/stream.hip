@@ -133,7 +133,7 @@ int mdgmi_stream_create(const mdgmi_format* fmt, double sigma2, int64_t buffer_n
     const GmiPlan pl = plan_gmi(fmt, buffer_n, 1, p);
     s->part_bytes = align_up(pl.part_bytes);
     s->ws_bytes = pl.total;
-    s->max_blocks = pl.cfg.blocks_per_snr;
+    s->max_blocks = (int)(pl.part_bytes / (kNPart * sizeof(double)));  // what the lanes' partial tables hold
     const size_t ybytes = (size_t)buffer_n * fmt->dim * (p == MDGMI_PATH_F64 ? sizeof(double) : sizeof(float));
     bool ok = hipStreamCreateWithFlags(&s->acc_stream, hipStreamNonBlocking) == hipSuccess;
     s->lane.assign(n_lanes, nullptr);
