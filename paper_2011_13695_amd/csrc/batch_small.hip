@@ -24,9 +24,13 @@ __device__ __forceinline__ void run_small_item(const BatchInst& D, int64_t s0, i
     small::load_image<DIM, NG>(img, 4 * NG, a);
     HdAcc hd;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (int64_t b0 = s0 + 64 * wave; b0 < s1; b0 += 64 * kSmallWaves)
-        small::small_sample<DIM, NG, kModeGmi>(a, img, D.y, D.tx, b0 + lane, s1, D.s, D.X32, D.labels, nullptr,
-                                               acc, hd);
+    int64_t i = s0 + 64 * wave + lane;
+    small::SampleIn<DIM> in = small::load_sample<DIM, kModeGmi>(D.y, D.tx, i, s1);
+    for (int64_t b0 = s0 + 64 * wave; b0 < s1; b0 += 64 * kSmallWaves, i += 64 * kSmallWaves) {
+        const small::SampleIn<DIM> next = small::load_sample<DIM, kModeGmi>(D.y, D.tx, i + 64 * kSmallWaves, s1);
+        small::small_sample<DIM, NG, kModeGmi>(a, img, in, i, s1, D.s, D.X32, D.labels, nullptr, acc, hd);
+        in = next;
+    }
 }
 
 template <int DIM>
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void k_batch_small(const BatchIns
         __syncthreads();
         if (it >= i1) break;
         const BatchItem I = items[it];
-        const BatchInst D = insts[I.inst];
+        const BatchInst D = load_inst(insts + I.inst);
         CostAcc acc;
         if (D.dim == 1)
             run_small_dim<1>(D, I.s0, I.s1, acc);

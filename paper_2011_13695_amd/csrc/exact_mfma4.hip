@@ -47,8 +47,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const float* __restrict
     const int waves = kSmallThreads / 64;
     const int64_t nbat = (n + 63) / 64;
     // wave-uniform loop over batches of 64 consecutive samples
-    for (int64_t b = (int64_t)blockIdx.x * waves + wave; b < nbat; b += (int64_t)gridDim.x * waves)
-        small_sample<DIM, NG, MODE>(a, gimg, ys, txs, b * 64 + lane, n, s, X32, labels, llr, acc, hd, guard);
+    const int64_t step = (int64_t)gridDim.x * waves;
+    int64_t b = (int64_t)blockIdx.x * waves + wave;
+    SampleIn<DIM> in = load_sample<DIM, MODE>(ys, txs, b * 64 + lane, n);
+    for (; b < nbat; b += step) {
+        const SampleIn<DIM> next = load_sample<DIM, MODE>(ys, txs, (b + step) * 64 + lane, n);
+        small_sample<DIM, NG, MODE>(a, gimg, in, b * 64 + lane, n, s, X32, labels, llr, acc, hd, guard);
+        in = next;
+    }
     double* dst = part + ((int64_t)q_snr * gridDim.x + blockIdx.x) * (MODE == kModeHd ? kNPartHd : kNPart);
     if (MODE == kModeGmi || MODE == kModeMlGmi) block_reduce_store(acc, dst);
     if (MODE == kModeHd) block_reduce_store_hd(acc, hd, dst);

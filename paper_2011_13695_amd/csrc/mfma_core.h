@@ -666,7 +666,8 @@ __device__ __forceinline__ void mfma_coltile(const uint4* __restrict__ A, const 
             }
             // a class of some sample of this column lies too far for the
             // common offset (or y is not finite): second pass for the column
-            if (__ballot(!(smin >= ex2(kFarLog2))) != 0ull) {
+            // (columns past n, at y = 0, do not count)
+            if (__ballot(i < n && !(smin >= ex2(kFarLog2))) != 0ull) {
                 llr_far_pass<DIM, G, MAXHI, S>(A, ys, n, i, M, m, ntiles, s, X32, llr, p0, p1);
                 continue;
             }

@@ -194,13 +194,33 @@ __device__ __forceinline__ void load_image(const uint2* __restrict__ gimg, int M
     }
 }
 
+// What a lane reads of one sample: y and the sent row (not in LLR modes).
+// Lanes past n read the last sample (no branch around the loads).
+template <int DIM>
+struct SampleIn {
+    float y[DIM];
+    uint32_t row;
+};
+
+template <int DIM, int MODE>
+__device__ __forceinline__ SampleIn<DIM> load_sample(const float* __restrict__ ys, const uint32_t* __restrict__ txs,
+                                                     int64_t i, int64_t n) {
+    SampleIn<DIM> v;
+    const int64_t ic = i < n ? i : n - 1;
+#pragma unroll
+    for (int d = 0; d < DIM; d++) v.y[d] = ys[ic * DIM + d];
+    v.row = mode_is_llr(MODE) ? 0u : txs[ic];
+    return v;
+}
+
 // One sample per lane (all 64 lanes call it: the MFMAs need every lane;
-// lanes past n run on y = 0 and store nothing).
+// lanes past n run on y = 0 and store nothing). in: the sample's inputs,
+// loaded by the caller one batch ahead: a batch is 100-400 instructions, less
+// than the latency of its loads at the 2-5 waves per SIMD in flight.
 template <int DIM, int NG, int MODE>
 __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][Nk4<DIM>::value],
-                                             const uint2* __restrict__ gimg,
-                                             const float* __restrict__ ys, const uint32_t* __restrict__ txs,
-                                             int64_t i, int64_t n, float s, const float* __restrict__ X32,
+                                             const uint2* __restrict__ gimg, const SampleIn<DIM>& in, int64_t i,
+                                             int64_t n, float s, const float* __restrict__ X32,
                                              const uint32_t* __restrict__ labels, float* __restrict__ llr,
                                              CostAcc& acc, HdAcc& hd, float guard = 0.0f) {
     constexpr int NK = Nk4<DIM>::value;
@@ -212,14 +232,10 @@ __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][N
     constexpr bool ML = mode_is_ml(MODE), HD = MODE == kModeHd;
     const int lane = threadIdx.x & 63;
     const bool valid = i < n;
-    // lanes past n read the last sample (no branch around the loads) and
-    // then work on y = 0
-    const int64_t ic = valid ? i : n - 1;
     float yv[DIM], ys2 = 0.0f;
 #pragma unroll
     for (int d = 0; d < DIM; d++) {
-        const float v = ys[ic * DIM + d];
-        yv[d] = valid ? v : 0.0f;
+        yv[d] = valid ? in.y[d] : 0.0f;
         ys2 = fmaf(yv[d], yv[d], ys2);
     }
     // y beyond the fp16 range of its split (or not finite) takes the FP32
@@ -247,15 +263,14 @@ __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][N
     }
     float bank[CH], T[NC];
     float umax = -INFINITY;
-    // the sent point's row and label are fetched before the walk, its A
+    // the sent point's label is fetched before the walk, its A
     // operands halfway through it, so that their latency hides behind the
     // exponentials
     constexpr bool SENT = !mode_is_llr(MODE) && !ML;
     uint32_t row = 0u, slot = 0u;
     bool twin = false;  // hard decisions: a lower label shares the sent point
     if (SENT) {
-        const uint32_t r = txs[ic];
-        row = valid ? r : 0u;
+        row = valid ? in.row : 0u;
         const uint32_t lw = labels[row < (uint32_t)M ? row : 0u];
         slot = lw & kLabelMask;
         twin = HD && (lw & kTwinBit) != 0u;
@@ -333,13 +348,13 @@ __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][N
 #pragma unroll
             for (int k = 0; k < m; k++) redo = redo || fabsf(u1[k] - u0[k]) < guard;
         }
-        if (redo) class_max_u_f32<DIM>(yv, X32, M, m, s, u0, u1);
         if (!valid) return;
+        if (redo) class_max_u_f32<DIM>(yv, X32, M, m, s, u0, u1);
         if (MODE == kModeMlLlr) {
 #pragma unroll
             for (int k = 0; k < m; k++) llr[i * m + k] = finite ? (u1[k] - u0[k]) * (float)kLn2 : NAN;
         } else {
-            const uint32_t row = txs[i];
+            const uint32_t row = in.row;
             const bool row_ok = row < (uint32_t)M;
             const uint32_t slot = labels[row_ok ? row : 0u];
             float cg = 0.0f;
@@ -365,7 +380,7 @@ __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][N
         bool redo = !(smin >= ex2(kFarLog2)) || ybad;
 #pragma unroll
         for (int k = 0; k < m; k++) redo = redo || fabsf(out[k]) < guard;
-        if (redo) {
+        if (redo && valid) {
             float ls0[MDGMI_MAX_BITS], ls1[MDGMI_MAX_BITS], ltot, ti;
             exact_classes_f32<DIM>(yv, X32, M, m, s, -1, ls0, ls1, ltot, ti);
 #pragma unroll
@@ -408,6 +423,10 @@ __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][N
     // another point strictly nearer, or the sent point's coordinates shared
     // with a lower label (ties go to the lowest label)
     sym = umax > ui || twin ? 1.0f : 0.0f;
+    // (lanes past n stop before the per-class path: their y = 0 is far from
+    // row 0 at high SNR, and that path is M points twice over: 40-90 us behind
+    // the last batch of a call whose n is no multiple of 64)
+    if (!valid) return;
     if (ui >= kFarLog2 && !ybad) {
         cm = mi_cost2(tot, ui);
     } else {
@@ -425,7 +444,6 @@ __device__ __forceinline__ void small_sample(const half4 (&a)[Sets<NG>::value][N
         }
         cm = ltot + ti;
     }
-    if (!valid) return;
     if (!row_ok) cg = cm = NAN;
     acc.add(cg, cm);
     if (HD) {
