@@ -26,6 +26,24 @@ struct BatchInst {
     int img_u4;               // MFMA image size in 16-byte units
 };
 
+// A pointer read from memory has no address space the compiler could see, and
+// every access through it becomes a flat one, which takes the wait counters of
+// global memory and of LDS together (a load in flight is waited for at the
+// next LDS access). All of an instance's arrays are global memory: said here.
+template <class T>
+__device__ __forceinline__ const T* as_global(const T* p) {
+    return (const T*)(const __attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+__device__ __forceinline__ BatchInst load_inst(const BatchInst* p) {
+    BatchInst D = *p;
+    D.y = as_global(D.y);
+    D.tx = as_global(D.tx);
+    D.img = as_global((const char*)D.img);
+    D.X32 = as_global(D.X32);
+    D.labels = as_global(D.labels);
+    return D;
+}
+
 // A contiguous sample range of one instance.
 struct BatchItem {
     int32_t inst;

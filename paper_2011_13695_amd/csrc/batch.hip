@@ -1,8 +1,8 @@
 // Ragged batch: many (format, SNR, sample-count) instances in one persistent
 // launch.
 //
-// The host cuts every instance into items (contiguous sample ranges of about
-// kItemPairs sample*points each, aligned to the kernel's sample tiles) and
+// The host cuts every instance into items (contiguous sample ranges aligned to
+// the kernel's sample tiles, sized by item_costs below) and
 // lists them instance by instance: MFMA instances, then direct ones, largest
 // constellations first within each. One persistent grid per kind pulls items
 // from its own atomic counter; for each item a block
@@ -100,7 +100,7 @@ __global__ __launch_bounds__((KIND == kKindMfma ? kMfmaWaves : kDirectWaves) * 6
         __syncthreads();
         if (it >= i1) break;
         const BatchItem I = items[it];
-        const BatchInst D = insts[I.inst];
+        const BatchInst D = load_inst(insts + I.inst);
         CostAcc acc;
         if (KIND == kKindMfma) {
             const bool in_lds = D.img_u4 <= kLdsCapU4;
@@ -195,6 +195,33 @@ int batch_kind_for(const mdgmi_format* f, double s, int path) {
     return mfma_ok ? kKindMfma : kKindDirect;
 }
 
+// Work of one sample in points: the walk's M and the per-sample set-up and
+// end (about 6 tiles of 32 points on 32 x 32 tiles, 40 points on the other
+// two, from their instruction counts).
+static int64_t sample_cost(int kind, int M) { return M + (kind == kKindMfma ? 200 : 40); }
+
+// Item sizes per kind, in sample_cost units. A kind's blocks (one per CU for
+// 32 x 32 tiles, about two otherwise) each get at least eight items where the
+// batch is large enough, so that they end together; an item is at most
+// max_pairs, and at least several times its overheads (the pull, the operand
+// image, the FP64 reduction: 2-4 us) at the kind's rate per block (3e10 and
+// 9e9 points/s): a set of 748 items of 4x4-shape instances took 69, 49 and 47 us
+// with 30000, 100000 and 200000; one 8-D M = 512 instance 36, 45 and 70 us with
+// 400000, 800000 and 1600000. With max_pairs alone (2^22) an instance of 2e5
+// samples and M = 4 was one block's work. 48 instances of 1e3..2e5 samples,
+// M = 8..4096: 803 us then, 240 us now (the tail lanes' share of that: see
+// small_core.h).
+static void item_costs(const mdgmi_instance* inst, const std::vector<int>& kind, int64_t max_pairs,
+                       int64_t (&cost)[3]) {
+    int64_t total[3] = {0, 0, 0};
+    for (size_t q = 0; q < kind.size(); q++) total[kind[q]] += inst[q].n * sample_cost(kind[q], inst[q].fmt->M);
+    for (int k = 0; k < 3; k++) {
+        const int64_t blocks = (int64_t)device_cu_count() * (k == kKindMfma ? 1 : 2);
+        const int64_t least = k == kKindMfma ? 400000 : 200000;
+        cost[k] = std::max(least, std::min(max_pairs, total[k] / (8 * blocks)));
+    }
+}
+
 int plan_batch(const mdgmi_instance* inst, int n_inst, int path, int64_t item_pairs, BatchPlan& P) {
     P = BatchPlan();
     P.n_inst = n_inst;
@@ -244,6 +271,8 @@ int plan_batch(const mdgmi_instance* inst, int n_inst, int path, int64_t item_pa
         return inst[a].fmt->M > inst[b].fmt->M;
     });
     P.insts.resize(n_inst);
+    int64_t item_cost[3];
+    item_costs(inst, kind, item_pairs, item_cost);
     // items are grouped per instance in the order above; (first, end) per
     // caller instance lets the reduction find them
     std::vector<int32_t> first_of(n_inst), count_of(n_inst);
@@ -253,7 +282,7 @@ int plan_batch(const mdgmi_instance* inst, int n_inst, int path, int64_t item_pa
         const int64_t n = inst[q].n;
         const int align = kind[q] == kKindMfma ? 32 * kMfmaWaves
                                                : (kind[q] == kKindSmall ? kSmallItemAlign : 64 * kDirectWaves);
-        int64_t per = item_pairs / f->M;
+        int64_t per = item_cost[kind[q]] / sample_cost(kind[q], f->M);
         per = std::max<int64_t>(align, per / align * align);
         first_of[q] = (int32_t)P.items.size();
         for (int64_t s0 = 0; s0 < n; s0 += per) {
