@@ -20,10 +20,13 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "f64_math.h"
 
 namespace mdgmi {
 
 namespace {
+
+using namespace f64;
 
 constexpr int kF64Threads = 256;
 
@@ -36,87 +39,6 @@ __device__ __forceinline__ double dist2(const double* yv, const double* __restri
         d = fma(e, e, d);
     }
     return d;
-}
-
-// exp(-t) of t = d / (2 sigma2), d >= 0, as 2^-(d c) with c = log2(e) / (2 sigma2):
-// the argument is rounded to an integer n by adding 1.5 2^52 (whose low word
-// then holds n), the remainder f, |f| <= 1/2, is formed with c in two parts, so
-// that d c itself is never rounded, and n goes into the exponent field of
-// 2^f = 1 + f P(f), P the Chebyshev interpolant of degree 10 of (2^f - 1) / f
-// (within 2e-17 of 2^f). d is capped where the result is 2^-1000 (this also
-// takes NaN, to 2^-1000), so the field cannot wrap. About 1 ulp, 17
-// instructions; a table of 2^(k/32) and a series of degree 6 take as many, and
-// wait for the table.
-struct ExpScale {
-    double c, clo, dmax;
-};
-
-__device__ __forceinline__ ExpScale exp_scale(double inv2s2) {
-    const double l = 0x1.71547652b82fep+0, ll = 0x1.777d0ffda0d24p-56;  // log2(e), two parts
-    ExpScale e;
-    const double c = inv2s2 * l;
-    e.c = -c;
-    e.clo = -fma(inv2s2, ll, fma(inv2s2, l, -c));
-    e.dmax = 1000.0 / c;
-    return e;
-}
-
-constexpr double kExp2P[11] = {0x1.62e42fefa39efp-1,  0x1.ebfbdff82c598p-3,  0x1.c6b08d704a0c2p-5,
-                               0x1.3b2ab6fba1ddap-7,  0x1.5d87fe78a5276p-10, 0x1.430913096fd9fp-13,
-                               0x1.ffcbfc670dcd4p-17, 0x1.62bfd47773353p-20, 0x1.b524fae627834p-24,
-                               0x1.e6063f7217bc6p-28, 0x1.e9d3fe3952179p-32};
-
-__device__ __forceinline__ double exp_neg(double d, const ExpScale& s) {
-    const double magic = 6755399441055744.0;  // 1.5 2^52
-    d = fmin(d, s.dmax);
-    const double b = fma(d, s.c, magic);
-    const int n = __double2loint(b);
-    const double r = b - magic;
-    double f = fma(d, s.c, -r);
-    f = fma(d, s.clo, f);
-    double p = kExp2P[10];
-#pragma unroll
-    for (int k = 9; k >= 0; k--) p = fma(p, f, kExp2P[k]);
-    const double v = fma(f, p, 1.0);
-    return __hiloint2double(__double2hiint(v) + (n << 20), __double2loint(v));
-}
-
-// a / b for normal a, b and quotient (no range scaling): v_rcp_f64, two Newton
-// steps and a residual correction, within 1 ulp.
-__device__ __forceinline__ double fast_div(double a, double b) {
-    double r = __builtin_amdgcn_rcp(b);
-    r = fma(fma(-b, r, 1.0), r, r);
-    r = fma(fma(-b, r, 1.0), r, r);
-    const double q = a * r;
-    return fma(fma(-b, q, a), r, q);
-}
-
-// ln x for normal positive x, within about 1 ulp: x = 2^e v, v in [sqrt(1/2),
-// sqrt(2)), f = v - 1 (exact), s = f / (2 + f), and the atanh series ln v =
-// 2 s + s R(s^2) with R its terms from 2/3 s^2 on, to s^20 (the next is below
-// 3e-17), put together as f - s (f - R) so that s needs no extra digits. A
-// third of the library log's instructions, whose two-word arithmetic has no
-// use here: the sums it is taken of carry more than its rounding.
-__device__ __forceinline__ double ln_pos(double x) {
-    double v = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
-    int e = __builtin_amdgcn_frexp_exp(x);
-    const bool low = v < 0.70710678118654752440;
-    v = low ? v + v : v;
-    e -= low ? 1 : 0;
-    const double f = v - 1.0, s = fast_div(f, 2.0 + f), z = s * s;
-    double R = 2.0 / 21.0;
-#pragma unroll
-    for (int k = 19; k >= 3; k -= 2) R = fma(R, z, 2.0 / k);
-    R *= z;
-    const double de = (double)e;
-    // ln 2 in two parts, the first with 21 trailing zero bits: de times it is exact
-    return fma(de, 0x1.62e42fee00000p-1, f - fma(s, f - R, -de * 0x1.a39ef35793c76p-33));
-}
-
-// ln(1 + x) for x >= 0 up to the largest normal value
-__device__ __forceinline__ double ln1p_pos(double x) {
-    const double u = 1.0 + x;
-    return ln_pos(u) + (x - (u - 1.0)) * __builtin_amdgcn_rcp(u);
 }
 
 // Class sums S0[k] / S1[k] of the CHB low label bits from a bank of 2^CHB
