@@ -17,6 +17,7 @@
 #include "device_common.h"
 #include "mlp_gemm.h"
 #include "mlp_layout.h"
+#include "mlp_train.h"
 
 using mdgmi::mlp::GemmArgs;
 
@@ -213,25 +214,132 @@ struct CopyArgs {
     __bf16* wf[4];
 };
 
-__global__ void k_adam(AdamArgs a, CopyArgs c) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.P) return;
-    const float gi = a.g[i];
+// Adam on parameter i with gradient gi; returns its new value.
+__device__ __forceinline__ float adam_param(const AdamArgs& a, int64_t i, float gi) {
     const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * gi;
     const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * gi * gi;
     a.m[i] = mi;
     a.v[i] = vi;
     const float pi = a.p[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
     a.p[i] = pi;
+    return pi;
+}
+
+// The bf16 copies of weight j = o * in + k of layer l.
+__device__ __forceinline__ void copy_weight(const CopyArgs& c, int l, int64_t j, float pi) {
+    const int o = (int)(j / c.in[l]), k = (int)(j % c.in[l]);
+    const __bf16 b = (__bf16)pi;
+    c.w[l][j] = b;
+    c.wt[l][(int64_t)k * c.out[l] + o] = b;
+    if (c.fused) c.wf[l][fused::fused_offset(l, o, k, c.in[l])] = (__bf16)(pi * fused::layer_scale(l));
+}
+
+__global__ void k_adam(AdamArgs a, CopyArgs c) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.P) return;
+    const float pi = adam_param(a, i, a.g[i]);
     for (int l = 0; l < c.L; l++) {
         const int64_t j = i - c.woff[l];
         if (j < 0 || j >= (int64_t)c.out[l] * c.in[l]) continue;
-        const int o = (int)(j / c.in[l]), k = (int)(j % c.in[l]);
-        const __bf16 b = (__bf16)pi;
-        c.w[l][j] = b;
-        c.wt[l][(int64_t)k * c.out[l] + o] = b;
-        if (c.fused) c.wf[l][fused::fused_offset(l, o, k, c.in[l])] = (__bf16)(pi * fused::layer_scale(l));
+        copy_weight(c, l, j, pi);
     }
+}
+
+// The end of a fused training step, one launch: the weight gradients from
+// their split-K slices (in slice order; a thread takes four consecutive
+// weights of a layer), the bias gradients as row sums of D^T (one block each;
+// thread t adds samples 8t .. 8t + 7, then 8t + 2048 .. in turn, then a fixed
+// tree), the loss (one block), and, with `adam`, the Adam step on each
+// parameter where its gradient was formed.
+struct FinishArgs {
+    int adam, splits;
+    int64_t n;
+    const float* partial[4];  // [splits][out][in]
+    const __bf16* dt[4];      // [out][n]
+    int64_t boff[4];
+    int wfirst[5], bfirst[5]; // first block of each layer's weights, of its biases; totals
+    const double* lpart;
+    int nl;
+    double* loss;
+};
+
+__device__ __forceinline__ float block_sum256(float s) {
+    __shared__ float red[256];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    return red[0];
+}
+
+__global__ __launch_bounds__(256) void k_train_finish(FinishArgs f, AdamArgs a, CopyArgs c) {
+    float* grad = const_cast<float*>(a.g);
+    const int blk = blockIdx.x;
+    if (blk < f.wfirst[4]) {
+        int l = 0;
+        while (blk >= f.wfirst[l + 1]) l++;
+        const int64_t cnt = (int64_t)c.out[l] * c.in[l];
+        const int64_t j = 4 * ((int64_t)(blk - f.wfirst[l]) * 256 + threadIdx.x);
+        if (j >= cnt) return;
+        // out * in is a multiple of 4 and the layer's offset 16-byte aligned for this shape
+        float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int k = 0; k < f.splits; k++) {
+            const float4 v = *(const float4*)(f.partial[l] + (int64_t)k * cnt + j);
+            s.x += v.x;
+            s.y += v.y;
+            s.z += v.z;
+            s.w += v.w;
+        }
+        const int64_t i = c.woff[l] + j;
+        *(float4*)(grad + i) = s;
+        if (f.adam) {
+            const float gi[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+            for (int q = 0; q < 4; q++) copy_weight(c, l, j + q, adam_param(a, i + q, gi[q]));
+        }
+        return;
+    }
+    if (blk < f.wfirst[4] + f.bfirst[4]) {
+        const int r = blk - f.wfirst[4];
+        int l = 0;
+        while (r >= f.bfirst[l + 1]) l++;
+        const int64_t o = r - f.bfirst[l];
+        const __bf16* row = f.dt[l] + o * f.n;
+        const bool vec = f.n % 8 == 0 && ((uintptr_t)row & 15) == 0;
+        float s = 0.0f;
+        for (int64_t i = 8 * (int64_t)threadIdx.x; i < f.n; i += 8 * 256) {
+            if (vec) {
+                union {
+                    uint4 u;
+                    __bf16 h[8];
+                } p;
+                p.u = *(const uint4*)(row + i);
+#pragma unroll
+                for (int j = 0; j < 8; j++) s += (float)p.h[j];
+            } else {
+                for (int64_t j = i; j < i + 8 && j < f.n; j++) s += (float)row[j];
+            }
+        }
+        s = block_sum256(s);
+        if (threadIdx.x == 0) {
+            grad[f.boff[l] + o] = s;
+            if (f.adam) (void)adam_param(a, f.boff[l] + o, s);
+        }
+        return;
+    }
+    // the loss: thread t adds partials t, t + 256, ... in turn, then a fixed tree
+    __shared__ double red[256];
+    double s = 0.0;
+    for (int b = threadIdx.x; b < f.nl; b += 256) s += f.lpart[b];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *f.loss = red[0] / (double)f.n;
 }
 
 // bf16 copies W [out][in] and W^T [in][out] of every layer, one launch
@@ -251,6 +359,20 @@ __global__ void k_refresh(RefreshArgs a) {
     const __bf16 b = (__bf16)a.W[l][i];
     a.w[l][i] = b;
     a.wt[l][(int64_t)j * out + o] = b;
+}
+
+// Several split-K products with k-contiguous operands in one launch: the
+// tiles of all of them side by side in blockIdx.x, the slice in blockIdx.y.
+struct GemmSet {
+    GemmArgs g[4];
+    int first[5];   // first tile of each product, and their total
+};
+
+__global__ __launch_bounds__(256) void k_gemm_set(GemmSet s) {
+    int l = 0;
+    while ((int)blockIdx.x >= s.first[l + 1]) l++;
+    const int t = blockIdx.x - s.first[l], nx = (s.g[l].N + kTile - 1) / kTile;
+    gemm_tile<true, true, kEpiPartial>(s.g[l], t % nx, t / nx, blockIdx.y);
 }
 
 // ---- GEMM launch ----
@@ -279,6 +401,8 @@ struct MlpWs {
     int64_t x0, z[MDGMI_MLP_MAX_LAYERS], h[MDGMI_MLP_MAX_LAYERS], logits, d0, d1, dt, ht[MDGMI_MLP_MAX_LAYERS], part,
         lpart, total;
 };
+
+int64_t fused_train_bytes(const mdgmi_mlp* net, int64_t n);  // 0 for other shapes
 
 MlpWs mlp_ws(const mdgmi_mlp* net, int64_t n) {
     MlpWs w{};
@@ -310,7 +434,7 @@ MlpWs mlp_ws(const mdgmi_mlp* net, int64_t n) {
     o += al(splits * (int64_t)net->width * net->width * 4);
     w.lpart = o;
     o += al(1024 * 8);
-    w.total = o;
+    w.total = std::max(o, fused_train_bytes(net, n));
     return w;
 }
 
@@ -371,6 +495,111 @@ void refresh_all(mdgmi_mlp* net, hipStream_t st) {
     }
     hipLaunchKernelGGL(k_refresh, dim3((unsigned)((most + 255) / 256), (unsigned)net->L), dim3(256), 0, st, a);
     if (net->fused) (void)build_fused_weights(W, a.out, a.in, net->d_wf, st);
+}
+
+AdamArgs adam_args(const mdgmi_mlp* net, float lr, float beta1, float beta2, float eps) {
+    const float c1 = (float)(1.0 - std::pow((double)beta1, (double)net->step));
+    const float c2 = (float)(1.0 - std::pow((double)beta2, (double)net->step));
+    return {net->d_params, net->d_grad, net->d_m, net->d_v, net->P, lr, beta1, beta2, eps, c1, c2};
+}
+
+CopyArgs copy_args(const mdgmi_mlp* net) {
+    CopyArgs c{};
+    c.L = net->L;
+    c.fused = net->fused;
+    for (int l = 0; l < net->L; l++) {
+        c.woff[l] = net->woff[l];
+        c.out[l] = net->sizes[l + 1];
+        c.in[l] = net->sizes[l];
+        c.w[l] = net->d_w[l];
+        c.wt[l] = net->d_wt[l];
+        if (l < 4) c.wf[l] = net->d_wf[l];
+    }
+    return c;
+}
+
+// Workspace of the fused training pass.
+struct FusedWs {
+    int64_t ht[4], dt[4], part[4], lpart, total;
+};
+
+FusedWs fused_ws(const mdgmi_mlp* net, int64_t n) {
+    FusedWs w{};
+    int64_t o = 0;
+    const int64_t splits = (n + split_len(n) - 1) / split_len(n);
+    for (int l = 0; l < 4; l++) {
+        w.ht[l] = o;
+        o += al(n * net->sizes[l] * 2);
+        w.dt[l] = o;
+        o += al(n * net->sizes[l + 1] * 2);
+        w.part[l] = o;
+        o += al(splits * net->sizes[l] * net->sizes[l + 1] * 4);
+    }
+    w.lpart = o;
+    o += al((int64_t)train_pass_blocks(n) * 8);
+    w.total = o;
+    return w;
+}
+
+int64_t fused_train_bytes(const mdgmi_mlp* net, int64_t n) { return net->fused ? fused_ws(net, n).total : 0; }
+
+// Loss, gradient and (adam) the Adam step of a network of the fused shape,
+// three launches: the pass over the samples, the weight gradients' split-K
+// products of all layers, and their sums with everything per parameter.
+hipError_t fused_train(mdgmi_mlp* net, const float* x, const float* y, const float* snr_db, const float* target,
+                       int64_t n, double* loss, char* ws, const AdamArgs& aa, bool adam, hipStream_t st) {
+    const FusedWs w = fused_ws(net, n);
+    TrainPass tp{};
+    tp.x = x;
+    tp.y = y;
+    tp.snr_db = snr_db;
+    tp.target = target;
+    tp.n = n;
+    tp.in0 = net->sizes[0];
+    tp.out = net->sizes[4];
+    tp.lpart = (double*)(ws + w.lpart);
+    const int64_t slen = split_len(n);
+    FinishArgs f{};
+    f.adam = adam ? 1 : 0;
+    f.splits = (int)((n + slen - 1) / slen);
+    f.n = n;
+    GemmSet gs{};
+    for (int l = 0; l < 4; l++) {
+        const int in = net->sizes[l], out = net->sizes[l + 1];
+        tp.w[l] = net->d_w[l];
+        tp.wt[l] = net->d_wt[l];
+        tp.b[l] = net->d_params + net->boff[l];
+        tp.ht[l] = (__bf16*)(ws + w.ht[l]);
+        tp.dt[l] = (__bf16*)(ws + w.dt[l]);
+        // dW_l [out][in] = sum_s D[s][o] H[s][i], slices of the samples
+        GemmArgs& g = gs.g[l];
+        g.A = tp.dt[l];
+        g.a_sm = n;
+        g.a_sk = 1;
+        g.B = tp.ht[l];
+        g.b_sk = 1;
+        g.b_sn = n;
+        g.M = out;
+        g.N = in;
+        g.K = n;
+        g.k_per_split = slen;
+        g.C = (float*)(ws + w.part[l]);
+        gs.first[l + 1] = gs.first[l] + ((out + kTile - 1) / kTile) * ((in + kTile - 1) / kTile);
+        f.partial[l] = g.C;
+        f.dt[l] = tp.dt[l];
+        f.boff[l] = net->boff[l];
+        f.wfirst[l + 1] = f.wfirst[l] + (out * in + 1023) / 1024;
+        f.bfirst[l + 1] = f.bfirst[l] + out;
+    }
+    f.lpart = tp.lpart;
+    f.nl = train_pass_blocks(n);
+    f.loss = loss;
+    hipError_t e = launch_train_pass(tp, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gemm_set, dim3((unsigned)gs.first[4], (unsigned)f.splits), dim3(256), 0, st, gs);
+    hipLaunchKernelGGL(k_train_finish, dim3((unsigned)(f.wfirst[4] + f.bfirst[4] + 1)), dim3(256), 0, st, f, aa,
+                       copy_args(net));
+    return hipGetLastError();
 }
 
 bool ok_sizes(const int32_t* sizes, int L) {
@@ -518,6 +747,11 @@ int mdgmi_mlp_loss_grad(mdgmi_mlp* net, const float* x, const float* target_llr,
     if (ws_bytes < (size_t)w.total) return MDGMI_E_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char* base = (char*)ws;
+    if (net->fused)
+        return fused_train(net, x, nullptr, nullptr, target_llr, n, loss, base, adam_args(net, 0.0f, 0.9f, 0.999f, 1e-8f),
+                           false, st) == hipSuccess
+                   ? MDGMI_OK
+                   : MDGMI_E_HIP;
     if (forward(net, x, n, base, w, st, true) != hipSuccess) return MDGMI_E_HIP;
     const int L = net->L, outL = net->sizes[L];
     const int nb = (int)std::min<int64_t>(1024, (n * outL + 255) / 256);
@@ -585,20 +819,8 @@ int mdgmi_mlp_adam_step(mdgmi_mlp* net, float lr, float beta1, float beta2, floa
         return MDGMI_E_ARG;
     hipStream_t st = (hipStream_t)stream;
     net->step++;
-    const float c1 = (float)(1.0 - std::pow((double)beta1, (double)net->step));
-    const float c2 = (float)(1.0 - std::pow((double)beta2, (double)net->step));
-    const AdamArgs a{net->d_params, net->d_grad, net->d_m, net->d_v, net->P, lr, beta1, beta2, eps, c1, c2};
-    CopyArgs c{};
-    c.L = net->L;
-    c.fused = net->fused;
-    for (int l = 0; l < net->L; l++) {
-        c.woff[l] = net->woff[l];
-        c.out[l] = net->sizes[l + 1];
-        c.in[l] = net->sizes[l];
-        c.w[l] = net->d_w[l];
-        c.wt[l] = net->d_wt[l];
-        if (l < 4) c.wf[l] = net->d_wf[l];
-    }
+    const AdamArgs a = adam_args(net, lr, beta1, beta2, eps);
+    const CopyArgs c = copy_args(net);
     hipLaunchKernelGGL(k_adam, dim3((unsigned)((net->P + 255) / 256)), dim3(256), 0, st, a, c);
     return hipGetLastError() == hipSuccess ? MDGMI_OK : MDGMI_E_HIP;
 }
@@ -1029,6 +1251,13 @@ int mdgmi_mlp_train_step(mdgmi_mlp* net, const float* y, const float* snr_db, co
     hipStream_t st = (hipStream_t)stream;
     float* x = (float*)ws;
     char* mws = (char*)ws + al(n * net->sizes[0] * 4);
+    if (net->fused) {
+        net->step++;
+        return fused_train(net, nullptr, y, snr_db, llr_target, n, loss, mws, adam_args(net, lr, 0.9f, 0.999f, 1e-8f),
+                           true, st) == hipSuccess
+                   ? MDGMI_OK
+                   : MDGMI_E_HIP;
+    }
     if (features(y, n, net->sizes[0] - 1, snr_db, 0.0f, x, st) != hipSuccess) return MDGMI_E_HIP;
     int rc = mdgmi_mlp_loss_grad(net, x, llr_target, n, loss, mws, (size_t)mlp_ws(net, n).total, stream);
     if (rc != MDGMI_OK) return rc;

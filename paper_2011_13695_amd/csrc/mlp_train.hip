@@ -1,0 +1,261 @@
+// Forward and backward pass of the MLP demapper's training step for networks
+// [in <= 16, 256, 256, 256, out <= 32], one launch.
+//
+// A block takes 16 samples through all layers and back: activations and
+// back-propagated gradients go from layer to layer through LDS (bf16, the
+// rounding points of the layer-by-layer path), the pre-activations that GELU'
+// needs stay in the registers of the lanes that formed them, and only the
+// transposed copies [features][n] that the weight gradients contract over are
+// written out. Each layer is H^T = W H_prev^T (backward: D_prev^T = W^T D^T) on
+// v_mfma_f32_16x16x32_bf16, weights as the A operand straight from L2 (a lane's
+// operand is 16 consecutive bytes of a row), samples as the columns: wave w of
+// eight owns features 32 w .. 32 w + 31, two 16-row tiles, in every hidden
+// layer, forward and backward, so that Z meets its gradient in place. The 64
+// registers of a layer's weights are loaded one layer ahead.
+//
+// Sixteen samples per block because a step is small: 4096 samples are 256
+// blocks, one per CU. What bounds it is the weights' way from L2 (520 KB per
+// block) and the chain of nine dependent stages, not the 5.6 GFLOP.
+// @@TRAIN@@
+#include "device_common.h"
+#include "mlp_gemm.h"
+#include "mlp_train.h"
+
+namespace mdgmi {
+
+namespace {
+
+using mlp::bf16x8;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kS = 16;          // samples per block
+constexpr int kH = 256;         // hidden width
+constexpr int kP = kH + 8;      // LDS pitch of an activation row (bf16)
+constexpr int kPs = 40;         // ... of the narrow ones (features, output gradients)
+
+union Q8 {
+    bf16x8 v;
+    uint4 u;
+    __bf16 h[8];
+};
+union Q4 {
+    uint2 u;
+    __bf16 h[4];
+};
+
+// A operands of this wave's two row tiles of a [256][256] matrix.
+__device__ __forceinline__ void load_w(const __bf16* __restrict__ W, int f0, int col, int g, bf16x8 (&w)[2][8]) {
+#pragma unroll
+    for (int t = 0; t < 2; t++)
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+            w[t][k] = *(const bf16x8*)(W + (uint32_t)((f0 + 16 * t + col) * kH + 32 * k + 8 * g));
+}
+
+// A operand (K = 32) of rows r of a [rows][cols] matrix with cols <= 32, zero
+// past its edges.
+__device__ __forceinline__ bf16x8 load_narrow(const __bf16* __restrict__ W, int r, int rows, int cols, int g) {
+    Q8 q;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int k = 8 * g + i;
+        q.h[i] = r < rows && k < cols ? W[(uint32_t)(r * cols + k)] : (__bf16)0.0f;
+    }
+    return q.v;
+}
+
+__device__ __forceinline__ void mfma_layer(const bf16x8 (&w)[2][8], const __bf16* __restrict__ src, int col, int g,
+                                           f32x4 (&acc)[2]) {
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const bf16x8 b = *(const bf16x8*)(src + col * kP + 32 * k + 8 * g);
+#pragma unroll
+        for (int t = 0; t < 2; t++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][k], b, acc[t], 0, 0, 0);
+    }
+}
+
+// A lane's four consecutive features of its sample.
+__device__ __forceinline__ void put4(__bf16* dst, int col, int f, const float* v) {
+    Q4 q;
+#pragma unroll
+    for (int r = 0; r < 4; r++) q.h[r] = (__bf16)v[r];
+    *(uint2*)(dst + col * kP + f) = q.u;
+}
+
+// The block's [16][256] tile in src to dst [256][n] at sample s0: thread
+// (feature, half) stores eight samples, 16 bytes where n allows.
+__device__ __forceinline__ void store_t(const __bf16* __restrict__ src, __bf16* __restrict__ dst, int64_t n, int64_t s0) {
+    const int f = threadIdx.x & (kH - 1), h = threadIdx.x >> 8;
+    Q8 q;
+#pragma unroll
+    for (int j = 0; j < 8; j++) q.h[j] = src[(8 * h + j) * kP + f];
+    __bf16* p = dst + (int64_t)f * n + s0 + 8 * h;
+    if (n % 8 == 0) {  // then eight samples are all below n or none, and the rows are 16-byte aligned
+        if (s0 + 8 * h < n) *(uint4*)p = q.u;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            if (s0 + 8 * h + j < n) p[j] = q.h[j];
+    }
+}
+
+__global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
+    __shared__ __attribute__((aligned(16))) __bf16 sx[kS * kPs], sd[kS * kPs], sA[kS * kP], sB[kS * kP];
+    __shared__ float sz[kS * 33];
+    __shared__ double red[8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, g = lane >> 4, f0 = 32 * wave;
+    const int64_t n = a.n, s0 = (int64_t)blockIdx.x * kS;
+    const int in0 = a.in0, out = a.out;
+    double loss = 0.0;
+    bf16x8 wA[2][8], wB[2][8];
+    load_w(a.w[1], f0, col, g, wA);
+    // ---- features (K padded to 32 with zeros): one per thread
+    {
+        const int s = threadIdx.x >> 5, f = threadIdx.x & 31;
+        const int64_t i = s0 + s;
+        float v = 0.0f;
+        if (i < n && f < in0) {
+            if (a.x)
+                v = a.x[i * in0 + f];
+            else if (f < in0 - 1)
+                v = a.y[i * (in0 - 1) + f];
+            else  // in FP64 like the host-side scalar feature
+                v = (float)(((double)a.snr_db[i] - 9.5) / 4.5);
+        }
+        const __bf16 b = (__bf16)v;
+        sx[s * kPs + f] = b;
+        if (i < n && f < in0) a.ht[0][(int64_t)f * n + i] = b;
+    }
+    f32x4 z1[2], z2[2], z3[2], acc[2];
+    bf16x8 w1[2];
+#pragma unroll
+    for (int t = 0; t < 2; t++) {
+        w1[t] = load_narrow(a.w[0], f0 + 16 * t + col, kH, in0, g);
+        z1[t] = *(const f32x4*)(a.b[0] + f0 + 16 * t + 4 * g);
+        z2[t] = *(const f32x4*)(a.b[1] + f0 + 16 * t + 4 * g);
+        z3[t] = *(const f32x4*)(a.b[2] + f0 + 16 * t + 4 * g);
+    }
+    auto gelu_out = [&](const f32x4 (&z)[2], __bf16* dst) {
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) v[r] = mlp::gelu_f(z[t][r]);
+            put4(dst, col, f0 + 16 * t + 4 * g, v);
+        }
+    };
+    auto grad_out = [&](const f32x4 (&z)[2], __bf16* dst) {
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) v[r] = acc[t][r] * mlp::gelu_grad_f(z[t][r]);
+            put4(dst, col, f0 + 16 * t + 4 * g, v);
+        }
+    };
+    __syncthreads();
+    // ---- layer 1
+    {
+        const bf16x8 b = *(const bf16x8*)(sx + col * kPs + 8 * g);
+#pragma unroll
+        for (int t = 0; t < 2; t++) z1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[t], b, z1[t], 0, 0, 0);
+    }
+    load_w(a.w[2], f0, col, g, wB);
+    gelu_out(z1, sA);
+    __syncthreads();
+    // ---- layer 2
+    mfma_layer(wA, sA, col, g, z2);
+    store_t(sA, a.ht[1], n, s0);
+    load_w(a.wt[2], f0, col, g, wA);
+    gelu_out(z2, sB);
+    __syncthreads();
+    // ---- layer 3
+    mfma_layer(wB, sB, col, g, z3);
+    store_t(sB, a.ht[2], n, s0);
+    load_w(a.wt[1], f0, col, g, wB);
+    gelu_out(z3, sA);
+    __syncthreads();
+    // ---- layer 4: logits, 16 rows per wave
+    store_t(sA, a.ht[3], n, s0);
+    if (16 * wave < out) {
+        f32x4 z4;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int o = 16 * wave + 4 * g + r;
+            z4[r] = o < out ? a.b[3][o] : 0.0f;
+        }
+        const int row = 16 * wave + col;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            Q8 q;
+            q.u = row < out ? *(const uint4*)(a.w[3] + row * kH + 32 * k + 8 * g) : make_uint4(0u, 0u, 0u, 0u);
+            const bf16x8 b = *(const bf16x8*)(sA + col * kP + 32 * k + 8 * g);
+            z4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q.v, b, z4, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++) sz[col * 33 + 16 * wave + 4 * g + r] = z4[r];
+    }
+    bf16x8 w4[2];
+#pragma unroll
+    for (int t = 0; t < 2; t++) w4[t] = load_narrow(a.wt[3], f0 + 16 * t + col, kH, out, g);
+    __syncthreads();
+    // ---- loss and its gradient: (sigmoid(z) - sigmoid(lambda)) / n
+    {
+        const int s = threadIdx.x >> 5, k = threadIdx.x & 31;
+        const int64_t i = s0 + s;
+        __bf16 d = (__bf16)0.0f;
+        if (i < n && k < out) {
+            const float z = sz[s * 33 + k];
+            const float p = 1.0f / (1.0f + expf(-a.target[i * out + k]));
+            const float q = 1.0f / (1.0f + expf(-z));
+            d = (__bf16)((q - p) / (float)n);
+            a.dt[3][(int64_t)k * n + i] = d;
+            const double sp = (z > 0.0f ? (double)z : 0.0) + log1p(exp(-(double)fabsf(z)));
+            loss += sp - (double)p * (double)z;
+        }
+        sd[s * kPs + k] = d;
+    }
+    __syncthreads();
+    // ---- gradients of the hidden layers, last to first
+    {
+        const bf16x8 b = *(const bf16x8*)(sd + col * kPs + 8 * g);
+#pragma unroll
+        for (int t = 0; t < 2; t++)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w4[t], b, (f32x4){0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+    }
+    grad_out(z3, sB);
+    __syncthreads();
+    acc[0] = acc[1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    mfma_layer(wA, sB, col, g, acc);
+    store_t(sB, a.dt[2], n, s0);
+    grad_out(z2, sA);
+    __syncthreads();
+    acc[0] = acc[1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    mfma_layer(wB, sA, col, g, acc);
+    store_t(sA, a.dt[1], n, s0);
+    grad_out(z1, sB);
+    __syncthreads();
+    store_t(sB, a.dt[0], n, s0);
+    // loss partial: a fixed tree per wave, then the waves in order
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) loss += __shfl_down(loss, off, 64);
+    if (lane == 0) red[wave] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < 8; w++) s += red[w];
+        a.lpart[blockIdx.x] = s;
+    }
+}
+
+}  // namespace
+
+int train_pass_blocks(int64_t n) { return (int)((n + kS - 1) / kS); }
+
+hipError_t launch_train_pass(const TrainPass& a, hipStream_t st) {
+    hipLaunchKernelGGL(k_train_pass, dim3((unsigned)train_pass_blocks(a.n)), dim3(512), 0, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace mdgmi
