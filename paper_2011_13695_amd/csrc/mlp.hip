@@ -31,8 +31,9 @@ struct mdgmi_mlp {
     float* d_v = nullptr;
     float* d_grad = nullptr;
     __bf16* d_w[MDGMI_MLP_MAX_LAYERS] = {nullptr};   // [out][in]
-    __bf16* d_wt[MDGMI_MLP_MAX_LAYERS] = {nullptr};  // [in][out]
+    __bf16* d_wt[MDGMI_MLP_MAX_LAYERS] = {nullptr};  // [in][out]; fused shapes: train_wt_offset
     __bf16* d_wf[4] = {nullptr};                     // fused-inference layout (fused shapes only)
+    __bf16* d_wo[4] = {nullptr};                     // layers 1..3: train_w_offset (fused shapes only)
     bool fused = false;
     int64_t step = 0;
     int device = 0;
@@ -212,6 +213,7 @@ struct CopyArgs {
     __bf16* w[MDGMI_MLP_MAX_LAYERS];
     __bf16* wt[MDGMI_MLP_MAX_LAYERS];
     __bf16* wf[4];
+    __bf16* wo[4];
 };
 
 // Adam on parameter i with gradient gi; returns its new value.
@@ -225,13 +227,33 @@ __device__ __forceinline__ float adam_param(const AdamArgs& a, int64_t i, float 
     return pi;
 }
 
+// The same on four consecutive parameters from a 16-byte aligned one.
+__device__ __forceinline__ void adam_param4(const AdamArgs& a, int64_t i, const float (&g)[4], float (&p)[4]) {
+    float4 m4 = *(const float4*)(a.m + i), v4 = *(const float4*)(a.v + i), p4 = *(const float4*)(a.p + i);
+    float* m = &m4.x;
+    float* v = &v4.x;
+    const float* po = &p4.x;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        m[q] = a.b1 * m[q] + (1.0f - a.b1) * g[q];
+        v[q] = a.b2 * v[q] + (1.0f - a.b2) * g[q] * g[q];
+        p[q] = po[q] - a.lr * (m[q] / a.c1) / (sqrtf(v[q] / a.c2) + a.eps);
+    }
+    *(float4*)(a.m + i) = m4;
+    *(float4*)(a.v + i) = v4;
+    *(float4*)(a.p + i) = make_float4(p[0], p[1], p[2], p[3]);
+}
+
 // The bf16 copies of weight j = o * in + k of layer l.
 __device__ __forceinline__ void copy_weight(const CopyArgs& c, int l, int64_t j, float pi) {
     const int o = (int)(j / c.in[l]), k = (int)(j % c.in[l]);
     const __bf16 b = (__bf16)pi;
     c.w[l][j] = b;
-    c.wt[l][(int64_t)k * c.out[l] + o] = b;
-    if (c.fused) c.wf[l][fused::fused_offset(l, o, k, c.in[l])] = (__bf16)(pi * fused::layer_scale(l));
+    c.wt[l][c.fused ? fused::train_wt_offset(l, o, k, c.out[l]) : (int64_t)k * c.out[l] + o] = b;
+    if (c.fused) {
+        c.wf[l][fused::fused_offset(l, o, k, c.in[l])] = (__bf16)(pi * fused::layer_scale(l));
+        if (l > 0) c.wo[l][fused::train_w_offset(o, k)] = b;
+    }
 }
 
 __global__ void k_adam(AdamArgs a, CopyArgs c) {
@@ -280,13 +302,18 @@ __global__ __launch_bounds__(256) void k_train_finish(FinishArgs f, AdamArgs a, 
     if (blk < f.wfirst[4]) {
         int l = 0;
         while (blk >= f.wfirst[l + 1]) l++;
-        const int64_t cnt = (int64_t)c.out[l] * c.in[l];
-        const int64_t j = 4 * ((int64_t)(blk - f.wfirst[l]) * 256 + threadIdx.x);
-        if (j >= cnt) return;
+        const int b = blk - f.wfirst[l], in = c.in[l];
+        const int64_t cnt = (int64_t)c.out[l] * in;
+        const bool tiled = l == 1 || l == 2;
+        // tiles of 16 outputs x 64 inputs in the 256 x 256 layers, else runs of 1024 weights
+        const int o = 16 * (b >> 2) + (threadIdx.x >> 4), k = 64 * (b & 3) + 4 * (threadIdx.x & 15);
+        const int64_t j = tiled ? (int64_t)o * in + k : 4 * ((int64_t)b * 256 + threadIdx.x);
+        if (j >= cnt) return;  // (never in a tile)
         // out * in is a multiple of 4 and the layer's offset 16-byte aligned for this shape
         float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        for (int k = 0; k < f.splits; k++) {
-            const float4 v = *(const float4*)(f.partial[l] + (int64_t)k * cnt + j);
+#pragma unroll 8
+        for (int q = 0; q < f.splits; q++) {
+            const float4 v = *(const float4*)(f.partial[l] + (int64_t)q * cnt + j);
             s.x += v.x;
             s.y += v.y;
             s.z += v.z;
@@ -294,10 +321,36 @@ __global__ __launch_bounds__(256) void k_train_finish(FinishArgs f, AdamArgs a, 
         }
         const int64_t i = c.woff[l] + j;
         *(float4*)(grad + i) = s;
-        if (f.adam) {
-            const float gi[4] = {s.x, s.y, s.z, s.w};
+        if (!f.adam) return;
+        const float gi[4] = {s.x, s.y, s.z, s.w};
+        float pn[4];
+        adam_param4(a, i, gi, pn);
+        if (!tiled) {
 #pragma unroll
-            for (int q = 0; q < 4; q++) copy_weight(c, l, j + q, adam_param(a, i + q, gi[q]));
+            for (int q = 0; q < 4; q++) copy_weight(c, l, j + q, pn[q]);
+            return;
+        }
+        // the copies in 8-byte runs (four consecutive inputs are neighbours in
+        // every layout), the transposed one through LDS in runs of 16:
+        // element by element they were 2-byte stores 512 bytes apart
+        __shared__ __attribute__((aligned(16))) __bf16 tile[64][24];
+        union {
+            uint2 u;
+            __bf16 h[4];
+        } w4;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            w4.h[q] = (__bf16)pn[q];
+            tile[4 * (threadIdx.x & 15) + q][threadIdx.x >> 4] = w4.h[q];
+        }
+        *(uint2*)(c.w[l] + j) = w4.u;
+        *(uint2*)(c.wf[l] + fused::fused_offset(l, o, k, in)) = w4.u;
+        *(uint2*)(c.wo[l] + fused::train_w_offset(o, k)) = w4.u;
+        __syncthreads();
+        if (threadIdx.x < 128) {
+            const int r = threadIdx.x >> 1, h = threadIdx.x & 1;
+            *(uint4*)(c.wt[l] + fused::train_wt_offset(l, 16 * (b >> 2) + 8 * h, 64 * (b & 3) + r, c.out[l])) =
+                *(const uint4*)&tile[r][8 * h];
         }
         return;
     }
@@ -348,7 +401,9 @@ struct RefreshArgs {
     const float* W[MDGMI_MLP_MAX_LAYERS];
     __bf16* w[MDGMI_MLP_MAX_LAYERS];
     __bf16* wt[MDGMI_MLP_MAX_LAYERS];
+    __bf16* wo[4];
     int out[MDGMI_MLP_MAX_LAYERS], in[MDGMI_MLP_MAX_LAYERS];
+    bool fused;
 };
 
 __global__ void k_refresh(RefreshArgs a) {
@@ -358,7 +413,8 @@ __global__ void k_refresh(RefreshArgs a) {
     const int o = (int)(i / in), j = (int)(i % in);
     const __bf16 b = (__bf16)a.W[l][i];
     a.w[l][i] = b;
-    a.wt[l][(int64_t)j * out + o] = b;
+    a.wt[l][a.fused ? fused::train_wt_offset(l, o, j, out) : (int64_t)j * out + o] = b;
+    if (a.fused && l > 0) a.wo[l][fused::train_w_offset(o, j)] = b;
 }
 
 // Several split-K products with k-contiguous operands in one launch: the
@@ -489,10 +545,12 @@ void refresh_all(mdgmi_mlp* net, hipStream_t st) {
         W[l] = a.W[l] = net->d_params + net->woff[l];
         a.w[l] = net->d_w[l];
         a.wt[l] = net->d_wt[l];
+        if (l < 4) a.wo[l] = net->d_wo[l];
         a.out[l] = net->sizes[l + 1];
         a.in[l] = net->sizes[l];
         most = std::max<int64_t>(most, (int64_t)a.out[l] * a.in[l]);
     }
+    a.fused = net->fused;
     hipLaunchKernelGGL(k_refresh, dim3((unsigned)((most + 255) / 256), (unsigned)net->L), dim3(256), 0, st, a);
     if (net->fused) (void)build_fused_weights(W, a.out, a.in, net->d_wf, st);
 }
@@ -514,6 +572,7 @@ CopyArgs copy_args(const mdgmi_mlp* net) {
         c.w[l] = net->d_w[l];
         c.wt[l] = net->d_wt[l];
         if (l < 4) c.wf[l] = net->d_wf[l];
+        if (l < 4) c.wo[l] = net->d_wo[l];
     }
     return c;
 }
@@ -566,7 +625,7 @@ hipError_t fused_train(mdgmi_mlp* net, const float* x, const float* y, const flo
     GemmSet gs{};
     for (int l = 0; l < 4; l++) {
         const int in = net->sizes[l], out = net->sizes[l + 1];
-        tp.w[l] = net->d_w[l];
+        tp.w[l] = l == 0 ? net->d_wf[0] : net->d_wo[l];
         tp.wt[l] = net->d_wt[l];
         tp.b[l] = net->d_params + net->boff[l];
         tp.ht[l] = (__bf16*)(ws + w.ht[l]);
@@ -588,7 +647,7 @@ hipError_t fused_train(mdgmi_mlp* net, const float* x, const float* y, const flo
         f.partial[l] = g.C;
         f.dt[l] = tp.dt[l];
         f.boff[l] = net->boff[l];
-        f.wfirst[l + 1] = f.wfirst[l] + (out * in + 1023) / 1024;
+        f.wfirst[l + 1] = f.wfirst[l] + (out * in + 1023) / 1024;  // 64 tiles of 16 x 64 in the hidden layers
         f.bfirst[l + 1] = f.bfirst[l] + out;
     }
     f.lpart = tp.lpart;
@@ -648,12 +707,18 @@ int mdgmi_mlp_create(const int32_t* sizes, int32_t n_layers, uint64_t seed, mdgm
               hipMalloc(&net->d_m, sizeof(float) * p) == hipSuccess &&
               hipMalloc(&net->d_v, sizeof(float) * p) == hipSuccess &&
               hipMalloc(&net->d_grad, sizeof(float) * p) == hipSuccess;
+    net->fused = fused_shape_ok(net->sizes, net->L);
     for (int l = 0; ok && l < n_layers; l++) {
         const int64_t cnt = (int64_t)sizes[l + 1] * sizes[l];
-        ok = hipMalloc(&net->d_w[l], 2 * cnt) == hipSuccess && hipMalloc(&net->d_wt[l], 2 * cnt) == hipSuccess;
+        const int64_t tcnt = net->fused && l == 3 ? fused::kTrainWt3Elems : cnt;
+        ok = hipMalloc(&net->d_w[l], 2 * cnt) == hipSuccess && hipMalloc(&net->d_wt[l], 2 * tcnt) == hipSuccess &&
+             hipMemset(net->d_wt[l], 0, 2 * tcnt) == hipSuccess;
     }
-    net->fused = fused_shape_ok(net->sizes, net->L);
-    for (int l = 0; ok && net->fused && l < 4; l++) ok = hipMalloc(&net->d_wf[l], fused_weight_bytes(l)) == hipSuccess;
+    for (int l = 0; ok && net->fused && l < 4; l++) {
+        const size_t ob = 2 * (size_t)(l == 3 ? fused::kTrainW3Elems : sizes[l + 1] * sizes[l]);
+        ok = hipMalloc(&net->d_wf[l], fused_weight_bytes(l)) == hipSuccess &&
+             (l == 0 || (hipMalloc(&net->d_wo[l], ob) == hipSuccess && hipMemset(net->d_wo[l], 0, ob) == hipSuccess));
+    }
     ok = ok && hipMemcpy(net->d_params, h.data(), sizeof(float) * p, hipMemcpyHostToDevice) == hipSuccess &&
          hipMemset(net->d_m, 0, sizeof(float) * p) == hipSuccess &&
          hipMemset(net->d_v, 0, sizeof(float) * p) == hipSuccess &&
@@ -680,8 +745,10 @@ int mdgmi_mlp_destroy(mdgmi_mlp* net) {
         (void)hipFree(net->d_w[l]);
         (void)hipFree(net->d_wt[l]);
     }
-    for (int l = 0; l < 4; l++)
+    for (int l = 0; l < 4; l++) {
         if (net->d_wf[l]) (void)hipFree(net->d_wf[l]);
+        if (net->d_wo[l]) (void)hipFree(net->d_wo[l]);
+    }
     delete net;
     return MDGMI_OK;
 }

@@ -42,5 +42,22 @@ __host__ __device__ inline int64_t fused_offset(int l, int o, int k, int in) {
     return (((int64_t)(o / 32) * n_kb + kb) * 64 + lane) * 8 + slot;
 }
 
+// Weights as the training pass reads them (mlp_train.hip): a matrix [rows][K]
+// as A operands of v_mfma_f32_16x16x32_bf16, [16-row tile][K / 32 step][lane][8],
+// lane 16 g + r holding row r's k = 8 g .. 8 g + 7 of the step: natural order, so
+// that the products accumulate as on the layer-by-layer path, bit for bit.
+__host__ __device__ inline int64_t operand_offset(int row, int k, int steps) {
+    return (((int64_t)(row / 16) * steps + k / 32) * 64 + k % 32 / 8 * 16 + row % 16) * 8 + k % 8;
+}
+
+// For the fused shape: W_l of layers 1..3 (rows = outputs, 8 steps), and W_l^T of
+// layers 1..3 (rows = inputs; 8 steps, the output layer's at most 32 outputs
+// one step, zero past the last). Layer 0's W^T has no use there (row-major).
+constexpr int kTrainW3Elems = 32 * 256, kTrainWt3Elems = 256 * 32;
+__host__ __device__ inline int64_t train_w_offset(int o, int k) { return operand_offset(o, k, 8); }
+__host__ __device__ inline int64_t train_wt_offset(int l, int o, int k, int out) {
+    return l == 0 ? (int64_t)k * out + o : operand_offset(k, o, l == 3 ? 1 : 8);
+}
+
 }  // namespace fused
 }  // namespace mdgmi

@@ -14,8 +14,8 @@ struct TrainPass {
     const float* target;   // [n][out] target LLRs
     int64_t n;
     int in0, out;
-    const __bf16* w[4];    // [out][in] per layer
-    const __bf16* wt[4];   // [in][out]
+    const __bf16* w[4];    // weights: layer 0 in the order of fused_offset, others of train_w_offset (mlp_layout.h)
+    const __bf16* wt[4];   // transposed, in the order of train_wt_offset
     const float* b[4];
     __bf16* ht[4];         // inputs of every layer, [in][n]
     __bf16* dt[4];         // gradients at every layer's output, [out][n]

@@ -18,6 +18,7 @@
 // block) and the chain of nine dependent stages, not the 5.6 GFLOP.
 // @@TRAIN@@
 #include "device_common.h"
+#include "f64_math.h"
 #include "mlp_gemm.h"
 #include "mlp_train.h"
 
@@ -43,32 +44,25 @@ union Q4 {
     __bf16 h[4];
 };
 
-// A operands of this wave's two row tiles of a [256][256] matrix.
-__device__ __forceinline__ void load_w(const __bf16* __restrict__ W, int f0, int col, int g, bf16x8 (&w)[2][8]) {
+// A operands of this wave's two row tiles of a 256 x 256 layer (mlp_layout.h):
+// 1 KiB per load and wave.
+__device__ __forceinline__ void load_w(const __bf16* __restrict__ W, int wave, int lane, bf16x8 (&w)[2][8]) {
 #pragma unroll
     for (int t = 0; t < 2; t++)
 #pragma unroll
-        for (int k = 0; k < 8; k++)
-            w[t][k] = *(const bf16x8*)(W + (uint32_t)((f0 + 16 * t + col) * kH + 32 * k + 8 * g));
+        for (int k = 0; k < 8; k++) w[t][k] = *(const bf16x8*)(W + (uint32_t)((((2 * wave + t) * 8 + k) * 64 + lane) * 8));
 }
 
-// A operand (K = 32) of rows r of a [rows][cols] matrix with cols <= 32, zero
-// past its edges.
-__device__ __forceinline__ bf16x8 load_narrow(const __bf16* __restrict__ W, int r, int rows, int cols, int g) {
-    Q8 q;
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const int k = 8 * g + i;
-        q.h[i] = r < rows && k < cols ? W[(uint32_t)(r * cols + k)] : (__bf16)0.0f;
-    }
-    return q.v;
+// The matching B operand of step k from an activation row.
+__device__ __forceinline__ bf16x8 load_b(const __bf16* __restrict__ src, int col, int g, int k) {
+    return *(const bf16x8*)(src + col * kP + 32 * k + 8 * g);
 }
 
 __device__ __forceinline__ void mfma_layer(const bf16x8 (&w)[2][8], const __bf16* __restrict__ src, int col, int g,
                                            f32x4 (&acc)[2]) {
 #pragma unroll
     for (int k = 0; k < 8; k++) {
-        const bf16x8 b = *(const bf16x8*)(src + col * kP + 32 * k + 8 * g);
+        const bf16x8 b = load_b(src, col, g, k);
 #pragma unroll
         for (int t = 0; t < 2; t++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][k], b, acc[t], 0, 0, 0);
     }
@@ -102,6 +96,7 @@ __device__ __forceinline__ void store_t(const __bf16* __restrict__ src, __bf16* 
 __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     __shared__ __attribute__((aligned(16))) __bf16 sx[kS * kPs], sd[kS * kPs], sA[kS * kP], sB[kS * kP];
     __shared__ float sz[kS * 33];
+    __shared__ uint4 sw4[1024];  // the output layer's weights
     __shared__ double red[8];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, g = lane >> 4, f0 = 32 * wave;
@@ -109,7 +104,7 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     const int in0 = a.in0, out = a.out;
     double loss = 0.0;
     bf16x8 wA[2][8], wB[2][8];
-    load_w(a.w[1], f0, col, g, wA);
+    load_w(a.w[1], wave, lane, wA);
     // ---- features (K padded to 32 with zeros): one per thread
     {
         const int s = threadIdx.x >> 5, f = threadIdx.x & 31;
@@ -127,12 +122,25 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
         sx[s * kPs + f] = b;
         if (i < n && f < in0) a.ht[0][(int64_t)f * n + i] = b;
     }
+    // this thread's element of the loss: sample and output
+    const int ls = threadIdx.x >> 5, lk = threadIdx.x & 31;
+    const int64_t li = s0 + ls;
+    const bool lok = li < n && lk < out;
+    const float target = lok ? a.target[li * out + lk] : 0.0f;
+#pragma unroll
+    for (int q = 0; q < 2; q++) sw4[512 * q + threadIdx.x] = ((const uint4*)a.w[3])[512 * q + threadIdx.x];
     f32x4 z1[2], z2[2], z3[2], acc[2];
-    bf16x8 w1[2];
+    bf16x8 w1[2], w4[2];
 #pragma unroll
     for (int t = 0; t < 2; t++) {
-        w1[t] = load_narrow(a.w[0], f0 + 16 * t + col, kH, in0, g);
-        z1[t] = *(const f32x4*)(a.b[0] + f0 + 16 * t + 4 * g);
+        // layer 1 (its copy is scaled by 1/4, and so are bias and result here:
+        // exact powers of two) has 16 inputs, lane groups 0 and 1
+        Q8 q;
+        q.u = make_uint4(0u, 0u, 0u, 0u);
+        if (g < 2) q.u = *(const uint4*)(a.w[0] + (uint32_t)((wave * 64 + 32 * g + 16 * t + col) * 8));
+        w1[t] = q.v;
+        w4[t] = *(const bf16x8*)(a.wt[3] + (uint32_t)(((2 * wave + t) * 64 + lane) * 8));
+        z1[t] = 0.25f * *(const f32x4*)(a.b[0] + f0 + 16 * t + 4 * g);
         z2[t] = *(const f32x4*)(a.b[1] + f0 + 16 * t + 4 * g);
         z3[t] = *(const f32x4*)(a.b[2] + f0 + 16 * t + 4 * g);
     }
@@ -159,21 +167,21 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     {
         const bf16x8 b = *(const bf16x8*)(sx + col * kPs + 8 * g);
 #pragma unroll
-        for (int t = 0; t < 2; t++) z1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[t], b, z1[t], 0, 0, 0);
+        for (int t = 0; t < 2; t++) z1[t] = 4.0f * __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[t], b, z1[t], 0, 0, 0);
     }
-    load_w(a.w[2], f0, col, g, wB);
+    load_w(a.w[2], wave, lane, wB);
     gelu_out(z1, sA);
     __syncthreads();
     // ---- layer 2
     mfma_layer(wA, sA, col, g, z2);
     store_t(sA, a.ht[1], n, s0);
-    load_w(a.wt[2], f0, col, g, wA);
+    load_w(a.wt[2], wave, lane, wA);
     gelu_out(z2, sB);
     __syncthreads();
     // ---- layer 3
     mfma_layer(wB, sB, col, g, z3);
     store_t(sB, a.ht[2], n, s0);
-    load_w(a.wt[1], f0, col, g, wB);
+    load_w(a.wt[1], wave, lane, wB);
     gelu_out(z3, sA);
     __syncthreads();
     // ---- layer 4: logits, 16 rows per wave
@@ -185,36 +193,24 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
             const int o = 16 * wave + 4 * g + r;
             z4[r] = o < out ? a.b[3][o] : 0.0f;
         }
-        const int row = 16 * wave + col;
 #pragma unroll
         for (int k = 0; k < 8; k++) {
             Q8 q;
-            q.u = row < out ? *(const uint4*)(a.w[3] + row * kH + 32 * k + 8 * g) : make_uint4(0u, 0u, 0u, 0u);
-            const bf16x8 b = *(const bf16x8*)(sA + col * kP + 32 * k + 8 * g);
-            z4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q.v, b, z4, 0, 0, 0);
+            q.u = sw4[(wave * 8 + k) * 64 + lane];
+            z4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q.v, load_b(sA, col, g, k), z4, 0, 0, 0);
         }
 #pragma unroll
         for (int r = 0; r < 4; r++) sz[col * 33 + 16 * wave + 4 * g + r] = z4[r];
     }
-    bf16x8 w4[2];
-#pragma unroll
-    for (int t = 0; t < 2; t++) w4[t] = load_narrow(a.wt[3], f0 + 16 * t + col, kH, out, g);
     __syncthreads();
     // ---- loss and its gradient: (sigmoid(z) - sigmoid(lambda)) / n
+    const float zl = sz[ls * 33 + lk];
+    const float pl = 1.0f / (1.0f + expf(-target));
     {
-        const int s = threadIdx.x >> 5, k = threadIdx.x & 31;
-        const int64_t i = s0 + s;
-        __bf16 d = (__bf16)0.0f;
-        if (i < n && k < out) {
-            const float z = sz[s * 33 + k];
-            const float p = 1.0f / (1.0f + expf(-a.target[i * out + k]));
-            const float q = 1.0f / (1.0f + expf(-z));
-            d = (__bf16)((q - p) / (float)n);
-            a.dt[3][(int64_t)k * n + i] = d;
-            const double sp = (z > 0.0f ? (double)z : 0.0) + log1p(exp(-(double)fabsf(z)));
-            loss += sp - (double)p * (double)z;
-        }
-        sd[s * kPs + k] = d;
+        const float q = 1.0f / (1.0f + expf(-zl));
+        const __bf16 d = lok ? (__bf16)((q - pl) / (float)n) : (__bf16)0.0f;
+        if (lok) a.dt[3][(int64_t)lk * n + li] = d;
+        sd[ls * kPs + lk] = d;
     }
     __syncthreads();
     // ---- gradients of the hidden layers, last to first
@@ -225,6 +221,12 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w4[t], b, (f32x4){0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
     }
     grad_out(z3, sB);
+    if (lok) {
+        const double sp = (zl > 0.0f ? (double)zl : 0.0) +
+                          f64::ln1p_pos(f64::exp_neg((double)fabsf(zl), f64::exp_scale_unit()));
+        loss = sp - (double)pl * (double)zl;
+        if (!(zl == zl)) loss = NAN;
+    }
     __syncthreads();
     acc[0] = acc[1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
     mfma_layer(wA, sB, col, g, acc);
