@@ -269,32 +269,20 @@ __global__ void k_adam(AdamArgs a, CopyArgs c) {
 
 // The end of a fused training step, one launch: the weight gradients from
 // their split-K slices (in slice order; a thread takes four consecutive
-// weights of a layer), the bias gradients as row sums of D^T (one block each;
-// thread t adds samples 8t .. 8t + 7, then 8t + 2048 .. in turn, then a fixed
-// tree), the loss (one block), and, with `adam`, the Adam step on each
+// weights of a layer), the bias gradients as sums of D over the samples (one
+// block per 16 of them), the loss (one block), and, with `adam`, the Adam step on each
 // parameter where its gradient was formed.
 struct FinishArgs {
     int adam, splits;
     int64_t n;
     const float* partial[4];  // [splits][out][in]
-    const __bf16* dt[4];      // [out][n]
+    const float* dsum[4];     // as TrainPass
     int64_t boff[4];
     int wfirst[5], bfirst[5]; // first block of each layer's weights, of its biases; totals
     const double* lpart;
     int nl;
     double* loss;
 };
-
-__device__ __forceinline__ float block_sum256(float s) {
-    __shared__ float red[256];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    return red[0];
-}
 
 __global__ __launch_bounds__(256) void k_train_finish(FinishArgs f, AdamArgs a, CopyArgs c) {
     float* grad = const_cast<float*>(a.g);
@@ -358,25 +346,32 @@ __global__ __launch_bounds__(256) void k_train_finish(FinishArgs f, AdamArgs a, 
         const int r = blk - f.wfirst[4];
         int l = 0;
         while (r >= f.bfirst[l + 1]) l++;
-        const int64_t o = r - f.bfirst[l];
-        const __bf16* row = f.dt[l] + o * f.n;
-        const bool vec = f.n % 8 == 0 && ((uintptr_t)row & 15) == 0;
-        float s = 0.0f;
-        for (int64_t i = 8 * (int64_t)threadIdx.x; i < f.n; i += 8 * 256) {
-            if (vec) {
-                union {
-                    uint4 u;
-                    __bf16 h[8];
-                } p;
-                p.u = *(const uint4*)(row + i);
+        // 16 features: sum t of 256 adds the pass's sums t, t + 256, ... in turn,
+        // then a fixed tree over t
+        __shared__ float sums[256][17];
+        const int f0 = 16 * (r - f.bfirst[l]), width = 16 * (f.bfirst[l + 1] - f.bfirst[l]);
+        const int x = threadIdx.x & 15;
+        const int64_t nt = 2 * ((f.n + 15) / 16);
+        const float* src = f.dsum[l] + f0 + x;
+        const int t0 = threadIdx.x >> 4;
+        float part[16] = {};
+        for (int64_t q = t0; q < nt; q += 256) {  // sixteen loads at a time
+            float v[16];
 #pragma unroll
-                for (int j = 0; j < 8; j++) s += (float)p.h[j];
-            } else {
-                for (int64_t j = i; j < i + 8 && j < f.n; j++) s += (float)row[j];
-            }
+            for (int i = 0; i < 16; i++) v[i] = q + 16 * i < nt ? src[(q + 16 * i) * width] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; i++) part[i] += v[i];
         }
-        s = block_sum256(s);
-        if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) sums[t0 + 16 * i][x] = part[i];
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            for (int e = threadIdx.x; e < 16 * w; e += 256) sums[e >> 4][e & 15] += sums[(e >> 4) + w][e & 15];
+            __syncthreads();
+        }
+        const int o = f0 + threadIdx.x;
+        if (threadIdx.x < 16 && o < c.out[l]) {
+            const float s = sums[0][threadIdx.x];
             grad[f.boff[l] + o] = s;
             if (f.adam) (void)adam_param(a, f.boff[l] + o, s);
         }
@@ -415,20 +410,6 @@ __global__ void k_refresh(RefreshArgs a) {
     a.w[l][i] = b;
     a.wt[l][a.fused ? fused::train_wt_offset(l, o, j, out) : (int64_t)j * out + o] = b;
     if (a.fused && l > 0) a.wo[l][fused::train_w_offset(o, j)] = b;
-}
-
-// Several split-K products with k-contiguous operands in one launch: the
-// tiles of all of them side by side in blockIdx.x, the slice in blockIdx.y.
-struct GemmSet {
-    GemmArgs g[4];
-    int first[5];   // first tile of each product, and their total
-};
-
-__global__ __launch_bounds__(256) void k_gemm_set(GemmSet s) {
-    int l = 0;
-    while ((int)blockIdx.x >= s.first[l + 1]) l++;
-    const int t = blockIdx.x - s.first[l], nx = (s.g[l].N + kTile - 1) / kTile;
-    gemm_tile<true, true, kEpiPartial>(s.g[l], t % nx, t / nx, blockIdx.y);
 }
 
 // ---- GEMM launch ----
@@ -577,9 +558,11 @@ CopyArgs copy_args(const mdgmi_mlp* net) {
     return c;
 }
 
+int tiles32(int v) { return (v + 31) / 32; }
+
 // Workspace of the fused training pass.
 struct FusedWs {
-    int64_t ht[4], dt[4], part[4], lpart, total;
+    int64_t ht[4], dt[4], dsum[4], part[4], lpart, total;
 };
 
 FusedWs fused_ws(const mdgmi_mlp* net, int64_t n) {
@@ -587,10 +570,13 @@ FusedWs fused_ws(const mdgmi_mlp* net, int64_t n) {
     int64_t o = 0;
     const int64_t splits = (n + split_len(n) - 1) / split_len(n);
     for (int l = 0; l < 4; l++) {
+        const int64_t np = 16 * (int64_t)train_pass_blocks(n);
         w.ht[l] = o;
-        o += al(n * net->sizes[l] * 2);
+        o += al(np * tiles32(net->sizes[l]) * 64);
         w.dt[l] = o;
-        o += al(n * net->sizes[l + 1] * 2);
+        o += al(np * tiles32(net->sizes[l + 1]) * 64);
+        w.dsum[l] = o;
+        o += al(np / 8 * tiles32(net->sizes[l + 1]) * 32 * 4);
         w.part[l] = o;
         o += al(splits * net->sizes[l] * net->sizes[l + 1] * 4);
     }
@@ -622,7 +608,9 @@ hipError_t fused_train(mdgmi_mlp* net, const float* x, const float* y, const flo
     f.adam = adam ? 1 : 0;
     f.splits = (int)((n + slen - 1) / slen);
     f.n = n;
-    GemmSet gs{};
+    TrainDw dw{};
+    dw.blocks = train_pass_blocks(n);
+    dw.steps = slen / 16;
     for (int l = 0; l < 4; l++) {
         const int in = net->sizes[l], out = net->sizes[l + 1];
         tp.w[l] = l == 0 ? net->d_wf[0] : net->d_wo[l];
@@ -631,31 +619,20 @@ hipError_t fused_train(mdgmi_mlp* net, const float* x, const float* y, const flo
         tp.ht[l] = (__bf16*)(ws + w.ht[l]);
         tp.dt[l] = (__bf16*)(ws + w.dt[l]);
         // dW_l [out][in] = sum_s D[s][o] H[s][i], slices of the samples
-        GemmArgs& g = gs.g[l];
-        g.A = tp.dt[l];
-        g.a_sm = n;
-        g.a_sk = 1;
-        g.B = tp.ht[l];
-        g.b_sk = 1;
-        g.b_sn = n;
-        g.M = out;
-        g.N = in;
-        g.K = n;
-        g.k_per_split = slen;
-        g.C = (float*)(ws + w.part[l]);
-        gs.first[l + 1] = gs.first[l] + ((out + kTile - 1) / kTile) * ((in + kTile - 1) / kTile);
-        f.partial[l] = g.C;
-        f.dt[l] = tp.dt[l];
+        dw.layer[l] = {tp.dt[l], tp.ht[l], (float*)(ws + w.part[l]), out, in, tiles32(out), tiles32(in)};
+        dw.first[l + 1] = dw.first[l] + ((dw.layer[l].ot + 1) / 2) * ((dw.layer[l].it + 1) / 2);
+        f.partial[l] = dw.layer[l].part;
+        f.dsum[l] = tp.dsum[l] = (float*)(ws + w.dsum[l]);
         f.boff[l] = net->boff[l];
         f.wfirst[l + 1] = f.wfirst[l] + (out * in + 1023) / 1024;  // 64 tiles of 16 x 64 in the hidden layers
-        f.bfirst[l + 1] = f.bfirst[l] + out;
+        f.bfirst[l + 1] = f.bfirst[l] + 2 * tiles32(out);
     }
     f.lpart = tp.lpart;
     f.nl = train_pass_blocks(n);
     f.loss = loss;
     hipError_t e = launch_train_pass(tp, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gemm_set, dim3((unsigned)gs.first[4], (unsigned)f.splits), dim3(256), 0, st, gs);
+    if ((e = launch_train_dw(dw, f.splits, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_train_finish, dim3((unsigned)(f.wfirst[4] + f.bfirst[4] + 1)), dim3(256), 0, st, f, aa,
                        copy_args(net));
     return hipGetLastError();

@@ -115,15 +115,14 @@ __device__ __forceinline__ void load_tile_b(const GemmArgs& g, int64_t n0, int64
     }
 }
 
-// Output tile (by, bx) of 64 x 64, K slice bz.
 template <bool A_K_CONTIG, bool B_K_CONTIG, int EPI>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz) {
+__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
     __shared__ __attribute__((aligned(16))) __bf16 As[kTile * kLdsPitch];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[kTile * kLdsPitch];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;  // this wave's quarter
-    const int64_t m0 = (int64_t)by * kTile, n0 = (int64_t)bx * kTile;
-    const int64_t kb = (int64_t)bz * g.k_per_split;
+    const int64_t m0 = (int64_t)blockIdx.y * kTile, n0 = (int64_t)blockIdx.x * kTile;
+    const int64_t kb = (int64_t)blockIdx.z * g.k_per_split;
     const int64_t ke = kb + g.k_per_split < g.K ? kb + g.k_per_split : g.K;
     f32x16 acc = {};
     // The epilogue's inputs are fetched before the K loop, so that their
@@ -271,7 +270,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
             hv[r] = (__bf16)(v * gelu_grad_f(zp[r]));
             g.H[m * g.ldh + n] = hv[r];
         } else {
-            g.C[(int64_t)bz * g.M * g.N + m * g.N + n] = v;
+            g.C[(int64_t)blockIdx.z * g.M * g.N + m * g.N + n] = v;
         }
     }
     if constexpr (EPI == kEpiGeluBf16 || EPI == kEpiGeluGrad) {
@@ -298,11 +297,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
             }
         }
     }
-}
-
-template <bool A_K_CONTIG, bool B_K_CONTIG, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-    gemm_tile<A_K_CONTIG, B_K_CONTIG, EPI>(g, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 }  // namespace mlp

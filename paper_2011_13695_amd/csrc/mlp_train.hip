@@ -15,8 +15,10 @@
 //
 // Sixteen samples per block because a step is small: 4096 samples are 256
 // blocks, one per CU. What bounds it is the weights' way from L2 (520 KB per
-// block) and the chain of nine dependent stages, not the 5.6 GFLOP.
-// @@TRAIN@@
+// block, 64 bytes per cycle and CU at best: 8 k of its ~30 k cycles) and the chain of
+// nine dependent stages, not the 2.2 GFLOP. 4096 samples of 9-256-256-256-11: 17
+// us, and 34 us for the whole step of three launches (115 us and 20 launches
+// layer by layer).
 #include "device_common.h"
 #include "f64_math.h"
 #include "mlp_gemm.h"
@@ -76,21 +78,21 @@ __device__ __forceinline__ void put4(__bf16* dst, int col, int f, const float* v
     *(uint2*)(dst + col * kP + f) = q.u;
 }
 
-// The block's [16][256] tile in src to dst [256][n] at sample s0: thread
-// (feature, half) stores eight samples, 16 bytes where n allows.
-__device__ __forceinline__ void store_t(const __bf16* __restrict__ src, __bf16* __restrict__ dst, int64_t n, int64_t s0) {
-    const int f = threadIdx.x & (kH - 1), h = threadIdx.x >> 8;
+// The block's tile [16 samples][32 tiles features] in src (pitch p) as operands
+// of the weight-gradient products (TrainPass), 1 KiB per feature tile: thread
+// (f, h) stores samples 8 h .. 8 h + 7 of feature f. Samples past n are part of
+// it: their gradients are zero.
+// Returns their sum, in order.
+__device__ __forceinline__ float store_t(const __bf16* __restrict__ src, int p, int f, int h, __bf16* __restrict__ dst,
+                                         int tiles) {
     Q8 q;
 #pragma unroll
-    for (int j = 0; j < 8; j++) q.h[j] = src[(8 * h + j) * kP + f];
-    __bf16* p = dst + (int64_t)f * n + s0 + 8 * h;
-    if (n % 8 == 0) {  // then eight samples are all below n or none, and the rows are 16-byte aligned
-        if (s0 + 8 * h < n) *(uint4*)p = q.u;
-    } else {
+    for (int j = 0; j < 8; j++) q.h[j] = src[(8 * h + j) * p + f];
+    *(uint4*)(dst + (((int64_t)blockIdx.x * tiles + f / 32) * 64 + 32 * h + f % 32) * 8) = q.u;
+    float s = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 8; j++)
-            if (s0 + 8 * h + j < n) p[j] = q.h[j];
-    }
+    for (int j = 0; j < 8; j++) s += (float)q.h[j];
+    return s;
 }
 
 __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
@@ -102,6 +104,7 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     const int col = lane & 15, g = lane >> 4, f0 = 32 * wave;
     const int64_t n = a.n, s0 = (int64_t)blockIdx.x * kS;
     const int in0 = a.in0, out = a.out;
+    const int tf = threadIdx.x & (kH - 1), th = threadIdx.x >> 8;  // store_t's feature and half
     double loss = 0.0;
     bf16x8 wA[2][8], wB[2][8];
     load_w(a.w[1], wave, lane, wA);
@@ -118,9 +121,7 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
             else  // in FP64 like the host-side scalar feature
                 v = (float)(((double)a.snr_db[i] - 9.5) / 4.5);
         }
-        const __bf16 b = (__bf16)v;
-        sx[s * kPs + f] = b;
-        if (i < n && f < in0) a.ht[0][(int64_t)f * n + i] = b;
+        sx[s * kPs + f] = (__bf16)v;
     }
     // this thread's element of the loss: sample and output
     const int ls = threadIdx.x >> 5, lk = threadIdx.x & 31;
@@ -164,6 +165,7 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     };
     __syncthreads();
     // ---- layer 1
+    if (threadIdx.x < 64) (void)store_t(sx, kPs, threadIdx.x & 31, threadIdx.x >> 5, a.ht[0], 1);
     {
         const bf16x8 b = *(const bf16x8*)(sx + col * kPs + 8 * g);
 #pragma unroll
@@ -174,18 +176,18 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     __syncthreads();
     // ---- layer 2
     mfma_layer(wA, sA, col, g, z2);
-    store_t(sA, a.ht[1], n, s0);
+    (void)store_t(sA, kP, tf, th, a.ht[1], 8);
     load_w(a.wt[2], wave, lane, wA);
     gelu_out(z2, sB);
     __syncthreads();
     // ---- layer 3
     mfma_layer(wB, sB, col, g, z3);
-    store_t(sB, a.ht[2], n, s0);
+    (void)store_t(sB, kP, tf, th, a.ht[2], 8);
     load_w(a.wt[1], wave, lane, wB);
     gelu_out(z3, sA);
     __syncthreads();
     // ---- layer 4: logits, 16 rows per wave
-    store_t(sA, a.ht[3], n, s0);
+    (void)store_t(sA, kP, tf, th, a.ht[3], 8);
     if (16 * wave < out) {
         f32x4 z4;
 #pragma unroll
@@ -209,11 +211,13 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     {
         const float q = 1.0f / (1.0f + expf(-zl));
         const __bf16 d = lok ? (__bf16)((q - pl) / (float)n) : (__bf16)0.0f;
-        if (lok) a.dt[3][(int64_t)lk * n + li] = d;
         sd[ls * kPs + lk] = d;
     }
     __syncthreads();
     // ---- gradients of the hidden layers, last to first
+    if (threadIdx.x < 64)
+        a.dsum[3][2 * (int64_t)blockIdx.x * 32 + threadIdx.x] =
+            store_t(sd, kPs, threadIdx.x & 31, threadIdx.x >> 5, a.dt[3], 1);
     {
         const bf16x8 b = *(const bf16x8*)(sd + col * kPs + 8 * g);
 #pragma unroll
@@ -230,15 +234,15 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     __syncthreads();
     acc[0] = acc[1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
     mfma_layer(wA, sB, col, g, acc);
-    store_t(sB, a.dt[2], n, s0);
+    a.dsum[2][(2 * (int64_t)blockIdx.x + th) * kH + tf] = store_t(sB, kP, tf, th, a.dt[2], 8);
     grad_out(z2, sA);
     __syncthreads();
     acc[0] = acc[1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
     mfma_layer(wB, sA, col, g, acc);
-    store_t(sA, a.dt[1], n, s0);
+    a.dsum[1][(2 * (int64_t)blockIdx.x + th) * kH + tf] = store_t(sA, kP, tf, th, a.dt[1], 8);
     grad_out(z1, sB);
     __syncthreads();
-    store_t(sB, a.dt[0], n, s0);
+    a.dsum[0][(2 * (int64_t)blockIdx.x + th) * kH + tf] = store_t(sB, kP, tf, th, a.dt[0], 8);
     // loss partial: a fixed tree per wave, then the waves in order
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) loss += __shfl_down(loss, off, 64);
@@ -251,9 +255,84 @@ __global__ __launch_bounds__(512) void k_train_pass(TrainPass a) {
     }
 }
 
+// Weight gradients of all layers, one wave per 64 x 64 tile of a layer's dW
+// [out][in] and slice of samples: dW = sum_s D[s][o] H[s][i] on
+// v_mfma_f32_32x32x16_bf16, both operands as the pass stored them, 1 KiB
+// contiguous per load, straight into registers (four of them per four MFMAs,
+// eight steps ahead: what the pass wrote comes from memory, not from this
+// die's L2, and a slice of 16 steps is two such trips). The general GEMM on row-major copies, through LDS, took
+// 10.4 us for these 640 tiles of 4096 samples; this 9.5 us, and the pass that
+// no longer scatters 32-byte pieces into rows 17.4 instead of 23.6 us.
+__global__ __launch_bounds__(64) void k_train_dw(TrainDw s) {
+    int l = 0;
+    while ((int)blockIdx.y >= s.first[l + 1]) l++;
+    const TrainDwLayer L = s.layer[l];
+    const int t = blockIdx.y - s.first[l], nx = (L.it + 1) / 2, by = t / nx, bx = t % nx;
+    const int lane = threadIdx.x;
+    const int64_t k0 = (int64_t)blockIdx.x * s.steps, left = s.blocks - k0;
+    const int nk = (int)(left < s.steps ? left : s.steps);  // >= 1
+    // a layer's only tile stands in for the second one (not stored)
+    const int o1 = 2 * by + 1 < L.ot ? 2 * by + 1 : 2 * by, i1 = 2 * bx + 1 < L.it ? 2 * bx + 1 : 2 * bx;
+    const __bf16* pa0 = L.dt + ((k0 * L.ot + 2 * by) * 64 + lane) * 8;
+    const __bf16* pa1 = L.dt + ((k0 * L.ot + o1) * 64 + lane) * 8;
+    const __bf16* pb0 = L.ht + ((k0 * L.it + 2 * bx) * 64 + lane) * 8;
+    const __bf16* pb1 = L.ht + ((k0 * L.it + i1) * 64 + lane) * 8;
+    const int sa = L.ot * 512, sb = L.it * 512;
+    constexpr int kAhead = 8;
+    bf16x8 a[kAhead][2], b[kAhead][2];
+    auto fetch = [&](int u, int k) {  // past the slice: its last step again, unused
+        const int64_t q = k < nk ? k : nk - 1;
+        a[u][0] = *(const bf16x8*)(pa0 + q * sa);
+        a[u][1] = *(const bf16x8*)(pa1 + q * sa);
+        b[u][0] = *(const bf16x8*)(pb0 + q * sb);
+        b[u][1] = *(const bf16x8*)(pb1 + q * sb);
+    };
+    mlp::f32x16 acc[2][2] = {};
+    auto product = [&](int u) {
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int u = 0; u < kAhead; u++) fetch(u, u);
+    int k = 0;
+    for (; k + kAhead < nk; k += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) {
+            product(u);
+            fetch(u, k + kAhead + u);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; u++)
+        if (k + u < nk) product(u);  // uniform
+    // lane holds rows 8 (r >> 2) + 4 (lane >> 5) + (r & 3) of column lane & 31
+    float* C = L.part + (int64_t)blockIdx.x * L.out * L.in;
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            if ((i == 1 && o1 == 2 * by) || (j == 1 && i1 == 2 * bx)) continue;
+            const int c = 32 * (2 * bx + j) + (lane & 31);
+            if (c >= L.in) continue;
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int o = 32 * (2 * by + i) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                if (o < L.out) C[o * L.in + c] = acc[i][j][r];
+            }
+        }
+}
+
 }  // namespace
 
 int train_pass_blocks(int64_t n) { return (int)((n + kS - 1) / kS); }
+
+hipError_t launch_train_dw(const TrainDw& s, int slices, hipStream_t st) {
+    hipLaunchKernelGGL(k_train_dw, dim3((unsigned)slices, (unsigned)s.first[4]), dim3(64), 0, st, s);
+    return hipGetLastError();
+}
 
 hipError_t launch_train_pass(const TrainPass& a, hipStream_t st) {
     hipLaunchKernelGGL(k_train_pass, dim3((unsigned)train_pass_blocks(a.n)), dim3(512), 0, st, a);
