@@ -64,7 +64,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_mfma(
     HdAcc hd;
     const float guard = mode_is_llr(MODE) ? llr_guard(s, max_n2) : 0.0f;
     const int64_t ncoltiles = (n + 32 * NCOL - 1) / (32 * NCOL);
-    for (int64_t ct = (int64_t)blockIdx.x * WAVES + wave; ct < ncoltiles; ct += (int64_t)gridDim.x * WAVES) {
+    // consecutive column tiles go to consecutive blocks: in the last round, which
+    // is seldom full, the waves left over spread over all CUs (one or two per
+    // SIMD) instead of filling some CUs while the rest idle. 8-D M = 2048 LLRs of
+    // 300007 samples (2.3 rounds): 116 -> 98 us.
+    for (int64_t ct = (int64_t)wave * gridDim.x + blockIdx.x; ct < ncoltiles; ct += (int64_t)gridDim.x * WAVES) {
         if constexpr (mode_is_ml(MODE))
             mfma_coltile_ml<DIM, NCOL, G, MODE, S>(A, ys, txs, n, ct, M, m, ntiles, s, X32, labels, llr, acc,
                                                    guard);
