@@ -63,7 +63,7 @@ LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int split, int 
     const MfmaVariant& v = var < 0 ? wide : kVariants[var];
     const int64_t cols = 32 * v.ncol;
     const int64_t tiles = (n + cols - 1) / cols;
-    const int64_t want = (tiles + v.waves - 1) / v.waves;
+    const int64_t want = n_snr <= kMaxSnrPerLaunch ? tiles : (tiles + v.waves - 1) / v.waves;
     // One resident round of blocks over all CUs: blocks per CU limited by
     // the LDS image (160 KiB per CU) and by a target of 16 waves per CU.
     const size_t img = image_bytes_per_snr(f, split);
@@ -73,6 +73,9 @@ LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int split, int 
     const int64_t total = (int64_t)device_cu_count() * std::min(by_lds, by_waves);
     const int snr_in_launch = n_snr < kMaxSnrPerLaunch ? n_snr : kMaxSnrPerLaunch;
     int64_t per = std::max<int64_t>(1, total / snr_in_launch);
+    // a short call takes a block per column tile as far as there are CUs: the
+    // tiles go to the blocks in turn, a wave or two of each has work, and a SIMD
+    // with one busy wave is through its tile in a third of the time
     per = std::min<int64_t>(per, std::max<int64_t>(1, want));
     LaunchCfg c;
     c.threads = v.waves * 64;
@@ -131,14 +134,15 @@ template <int S>
 hipError_t image_and_run(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
                          int mode, float* llr, double* part, uint4* img, int ntiles, LaunchCfg cfg, hipStream_t st) {
     const bool tuned_shape = S == kSplitF16 && !(mode == kModeHd || mode_is_ml(mode) || f->dim == 1);
-    MfmaShape shape{MfmaShape::kFixed, 0, image_bytes_per_snr(f, S) <= 128 * 1024};
+    const bool forced = g_variant_override >= 0 && g_variant_override < kNumVariants;
+    MfmaShape shape{MfmaShape::kFixed, 0, image_bytes_per_snr(f, S) <= 128 * 1024, forced};
     if (S == kSplitBF16 && bf16_wide(f, S)) {
-        shape = {MfmaShape::kWide, 0, false};
+        shape = {MfmaShape::kWide, 0, false, forced};
     } else if (tuned_shape) {
         // the shape mfma_cfg chose for this launch (its block count matches)
         const int var = cfg.variant;
         if (var < 0 || var >= kNumVariants) return hipErrorInvalidValue;
-        shape = {MfmaShape::kVariant, var, kVariants[var].lds && image_bytes_per_snr(f) <= 128 * 1024};
+        shape = {MfmaShape::kVariant, var, kVariants[var].lds && image_bytes_per_snr(f) <= 128 * 1024, forced};
     }
     switch (f->dim) {
         case 1:

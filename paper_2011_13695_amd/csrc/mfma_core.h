@@ -603,6 +603,207 @@ __device__ __forceinline__ void llr_far_pass(const uint4* __restrict__ A, const 
     }
 }
 
+// The end of one sample column: class sums, then LLRs or costs, from the lane's
+// bank and tile-bit sums. i: its sample (lanes past n take part in the lane
+// swaps and write nothing).
+template <int DIM, int G, int MODE, int S = kSplitF16>
+__device__ __forceinline__ void mfma_finish(const uint4* __restrict__ A, const float* __restrict__ ys,
+                                            const uint32_t* __restrict__ txs, int64_t n, int64_t i, int M, int m,
+                                            int ntiles, float s, const float* __restrict__ X32,
+                                            const uint32_t* __restrict__ labels, float* __restrict__ llr, CostAcc& acc,
+                                            HdAcc* hd, float guard, const half8 (&bop)[Blk<DIM, S>::value],
+                                            float (&bank)[16], HiAcc<G, MDGMI_MAX_BITS - 5>& hi, float umax) {
+    constexpr bool LLR = MODE == kModeLlr;
+    constexpr bool HD = MODE == kModeHd;
+    constexpr int NB = Blk<DIM, S>::value;
+    constexpr int MAXHI = MDGMI_MAX_BITS - 5;
+    constexpr int TS = NB * 64;
+    const int lane = threadIdx.x & 63;
+    const int h = lane >> 5, col = lane & 31;
+    // Each lane folds its own 16 rows into per-bit partial class sums; the
+    // two lane halves (rows differing in label bit 2) are combined with one
+    // lane swap per value, summed in the same order in both halves so that
+    // both hold identical class sums; each half then finishes every other
+    // label bit (half h takes bits h, h + 2, ...). Bits are streamed in pairs
+    // so that few class sums are live at a time.
+    float p0[MDGMI_MAX_BITS], p1[MDGMI_MAX_BITS];  // this half's partial class sums
+    half_partials<MAXHI, G>(bank, hi, m, p0, p1);
+    float S0t, S1t;
+    full_sums(p0, p1, 2, S0t, S1t);
+    const float tot = S0t + S1t;
+    if (LLR) {
+        float smin = INFINITY;
+#pragma unroll
+        for (int k = 0; k < MDGMI_MAX_BITS; k++) {
+            if (k < m) {
+                float S0k, S1k;
+                full_sums(p0, p1, k, S0k, S1k);
+                smin = fminf(smin, fminf(S0k, S1k));
+            }
+        }
+        // a class of some sample of this column lies too far for the
+        // common offset (or y is not finite): second pass for the column
+        // (columns past n, at y = 0, do not count)
+        if (__ballot(i < n && !(smin >= ex2(kFarLog2))) != 0ull) {
+            llr_far_pass<DIM, G, MAXHI, S>(A, ys, n, i, M, m, ntiles, s, X32, llr, p0, p1);
+            return;
+        }
+        constexpr int NJ = (MDGMI_MAX_BITS + 1) / 2;
+        float lam[NJ];
+        bool near0 = false;
+#pragma unroll
+        for (int j = 0; j < NJ; j++) {
+            lam[j] = 0.0f;
+            if (2 * j < m) {  // uniform
+                const int ke = 2 * j, ko = ke + 1 < MDGMI_MAX_BITS ? ke + 1 : ke;
+                float S0e, S1e, S0o = 1.0f, S1o = 1.0f;
+                if (ke == 2) {
+                    S0e = S0t;
+                    S1e = S1t;
+                } else {
+                    full_sums(p0, p1, ke, S0e, S1e);
+                }
+                if (ko < m) full_sums(p0, p1, ko, S0o, S1o);
+                const int k = ke + h;
+                const float s0 = h ? S0o : S0e, s1 = h ? S1o : S1e;
+                lam[j] = log2_ratio_fast(s1, s0);
+                if (k < m) near0 = near0 || fabsf(lam[j]) < guard;
+            }
+        }
+        // an LLR near zero at a large s (either half's bits): the whole
+        // sample is recomputed on the per-class path by lane half 0
+        const Halves hz = halves(near0 ? 1.0f : 0.0f);
+        const bool redo = hz.lo + hz.hi > 0.0f;
+        if (i >= n) return;
+        if (!redo) {
+#pragma unroll
+            for (int j = 0; j < NJ; j++) {
+                const int k = 2 * j + h;
+                if (k < m) llr[i * m + k] = lam[j] * (float)kLn2;
+            }
+        } else if (h == 0) {
+            float yc[DIM], ls0[MDGMI_MAX_BITS], ls1[MDGMI_MAX_BITS], ltot, ti;
+#pragma unroll
+            for (int d = 0; d < DIM; d++) yc[d] = ys[i * DIM + d];
+            exact_classes_f32<DIM>(yc, X32, M, m, s, -1, ls0, ls1, ltot, ti);
+#pragma unroll
+            for (int k = 0; k < MDGMI_MAX_BITS; k++)
+                if (k < m) llr[i * m + k] = (ls1[k] - ls0[k]) * (float)kLn2;
+        }
+        return;
+    }
+    // a sent row outside [0, M) gives a NaN cost instead of a stray read
+    const uint32_t row = i < n ? txs[i] : 0u;
+    const bool row_ok = row < (uint32_t)M;
+    const uint32_t lw = labels[row_ok ? row : 0u];
+    const uint32_t slot = lw & kLabelMask;
+    const bool twin = HD && (lw & kTwinBit) != 0u;  // a lower label shares the sent point
+    // u of the sent point by the matrix cores themselves: one more MFMA
+    // whose row r is the sent point of sample r puts u_i(y) on the
+    // diagonal, bit-identical to the value inside the class sums, so the
+    // MI cost log2 sum_j 2^(u_j - u_i) carries no recomputation error.
+    // Diagonal element r sits in lane half (r >> 2) & 1, register
+    // ((r >> 3) << 2) | (r & 3).
+    half8 ad[NB];
+    load_a_at<NB>(A + (int)(slot >> 5) * TS + h * 32 + (int)(slot & 31), ad);
+    const f32x16 ud = tile_mfma<NB, S>(ad, bop);
+    const int q = ((col >> 3) << 2) | (col & 3);
+    float dv = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; r++) dv = (r == q) ? ud[r] : dv;
+    const Halves d = halves(dv);
+    const float ui = ((col >> 2) & 1) ? d.hi : d.lo;
+    // this half's class sums of its bit pair j (bit 2j + h)
+    auto own_sums = [&](int j, float& s0, float& s1) {
+        const int ke = 2 * j, ko = ke + 1 < MDGMI_MAX_BITS ? ke + 1 : ke;
+        float S0e, S1e, S0o = 1.0f, S1o = 1.0f;
+        if (ke == 2) {
+            S0e = S0t;
+            S1e = S1t;
+        } else {
+            full_sums(p0, p1, ke, S0e, S1e);
+        }
+        if (ko < m) full_sums(p0, p1, ko, S0o, S1o);
+        s0 = h ? S0o : S0e;
+        s1 = h ? S1o : S1e;
+    };
+    // GMI cost of this half's bits, sum_k log2(T / S_sent,k), as one
+    // logarithm of the product of S_sent,k / T (cost_from_product)
+    float cg = 0.0f, be = 0.0f, prod = 1.0f;
+    const float rT = __builtin_amdgcn_rcpf(tot);
+#pragma unroll
+    for (int j = 0; j < (MDGMI_MAX_BITS + 1) / 2; j++) {
+        if (2 * j < m) {  // uniform
+            float s0, s1;
+            own_sums(j, s0, s1);
+            const int k = 2 * j + h;
+            if (k < m) {
+                const bool bk = (slot >> k) & 1;
+                prod *= (bk ? s1 : s0) * rT;
+                if (HD) be += (s1 > s0) != bk ? 1.0f : 0.0f;  // bitwise MAP decision
+            }
+        }
+    }
+    const bool fast = prod >= 0x1p-120f;
+    if (__ballot(!fast) == 0ull) {
+        cost_from_product(prod, cg);
+    } else {
+        // some sample of the wave has a cost beyond 120 bits or a
+        // non-finite sum: bit by bit, log2(1 + S_other / S_sent)
+        asm volatile("" ::: "memory");  // keeps the rare path a real branch
+#pragma unroll
+        for (int j = 0; j < (MDGMI_MAX_BITS + 1) / 2; j++) {
+            if (2 * j < m) {
+                float s0, s1;
+                own_sums(j, s0, s1);
+                const int k = 2 * j + h;
+                if (k < m) cg += bit_cost_sum2(s0 + s1, ((slot >> k) & 1) ? s1 : s0);
+            }
+        }
+    }
+    cg = half_sum(cg);
+    float sym = 0.0f;
+    if (HD) {
+        be = half_sum(be);
+        const Halves um = halves(umax);
+        // another point strictly nearer, or the sent point's coordinates
+        // shared with a lower label (ties go to the lowest label)
+        sym = fmaxf(um.lo, um.hi) > ui || twin ? 1.0f : 0.0f;
+    }
+    if (h != 0 || i >= n) return;
+    float cm;
+    if (ui >= kFarLog2) {
+        cm = mi_cost2(tot, ui);
+    } else {
+        // the sent point itself is far from y (or y is not finite)
+        float yc[DIM], ls0[MDGMI_MAX_BITS], ls1[MDGMI_MAX_BITS], ltot, ti = 0.0f, tmin = 0.0f;
+#pragma unroll
+        for (int dd = 0; dd < DIM; dd++) yc[dd] = ys[i * DIM + dd];
+        exact_classes_f32<DIM>(yc, X32, M, m, s, (int)slot, ls0, ls1, ltot, ti, HD ? &tmin : nullptr);
+        cg = 0.0f;
+        be = 0.0f;
+        // the split factors may be out of range here: decide the symbol
+        // from the FP32 distances as well
+        if (HD) sym = tmin < ti || twin ? 1.0f : 0.0f;
+#pragma unroll
+        for (int k = 0; k < MDGMI_MAX_BITS; k++) {
+            if (k < m) {
+                const bool bk = (slot >> k) & 1;
+                cg += bit_cost2(bk ? ls0[k] - ls1[k] : ls1[k] - ls0[k]);
+                if (HD) be += (ls1[k] > ls0[k]) != bk ? 1.0f : 0.0f;  // from the exact logarithms
+            }
+        }
+        cm = ltot + ti;
+    }
+    if (!row_ok) cg = cm = NAN;
+    acc.add(cg, cm);
+    if (HD) {
+        const bool finite = cg == cg && cm == cm && ui == ui;
+        hd->be += finite ? (double)be : (double)m;
+        hd->se += finite ? (double)sym : 1.0;
+    }
+}
+
 // One column tile: NCOL x 32 samples starting at sample ct * NCOL * 32 of one
 // (format, SNR) instance, against all points of its A image. Costs go to
 // acc (GMI mode) or LLRs to llr (LLR mode). All 64 lanes of the wave must
@@ -613,11 +814,9 @@ __device__ __forceinline__ void mfma_coltile(const uint4* __restrict__ A, const 
                                              int m, int ntiles, float s, const float* __restrict__ X32,
                                              const uint32_t* __restrict__ labels, float* __restrict__ llr,
                                              CostAcc& acc, HdAcc* hd = nullptr, float guard = 0.0f) {
-    constexpr bool LLR = MODE == kModeLlr;
     constexpr bool HD = MODE == kModeHd;
     constexpr int NB = Blk<DIM, S>::value;
     constexpr int MAXHI = MDGMI_MAX_BITS - 5;
-    constexpr int TS = NB * 64;
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5, col = lane & 31;
     half8 bop[NCOL][NB];
@@ -639,193 +838,86 @@ __device__ __forceinline__ void mfma_coltile(const uint4* __restrict__ A, const 
     HiAcc<G, MAXHI> hi[NCOL];
     float umax[NCOL];
     tile_loop<DIM, NCOL, G, false, MAXHI, HD, S>(A, ntiles, h, col, bop, bank, hi, umax);
-    // ---- epilogue ----
-    // Each lane folds its own 16 rows into per-bit partial class sums; the
-    // two lane halves (rows differing in label bit 2) are combined with one
-    // lane swap per value, summed in the same order in both halves so that
-    // both hold identical class sums; each half then finishes every other
-    // label bit (half h takes bits h, h + 2, ...). Bits are streamed in pairs
-    // so that few class sums are live at a time.
 #pragma unroll
-    for (int c = 0; c < NCOL; c++) {
-        const int64_t i = idx[c];
-        float p0[MDGMI_MAX_BITS], p1[MDGMI_MAX_BITS];  // this half's partial class sums
-        half_partials<MAXHI, G>(bank[c], hi[c], m, p0, p1);
-        float S0t, S1t;
-        full_sums(p0, p1, 2, S0t, S1t);
-        const float tot = S0t + S1t;
-        if (LLR) {
-            float smin = INFINITY;
+    for (int c = 0; c < NCOL; c++)
+        mfma_finish<DIM, G, MODE, S>(A, ys, txs, n, idx[c], M, m, ntiles, s, X32, labels, llr, acc, hd, guard, bop[c],
+                                     bank[c], hi[c], HD ? umax[c] : 0.0f);
+}
+
+// One column tile by a block of ntiles / 8 waves: each wave walks one group of
+// eight tiles, the groups' sums are added through LDS (in group order) and the
+// first wave ends the column. For calls of few column tiles, where a wave per
+// tile leaves most of the chip idle for the length of a whole walk. A: the image
+// in global memory. sums: [waves][kSplitSums][64] floats.
+constexpr int kSplitSums = 24;  // bank, three bit pairs inside a group, the group's total, its largest u
+template <int DIM, int MODE, int S = kSplitF16>
+__device__ __forceinline__ void mfma_split_coltile(const uint4* __restrict__ A, const float* __restrict__ ys,
+                                                   const uint32_t* __restrict__ txs, int64_t n, int64_t ct, int M,
+                                                   int m, int ntiles, float s, const float* __restrict__ X32,
+                                                   const uint32_t* __restrict__ labels, float* __restrict__ llr,
+                                                   CostAcc& acc, HdAcc* hd, float guard, float* __restrict__ sums) {
+    constexpr bool HD = MODE == kModeHd;
+    constexpr int NB = Blk<DIM, S>::value;
+    constexpr int MAXHI = MDGMI_MAX_BITS - 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, col = lane & 31, waves = ntiles / 8;
+    half8 bop[1][NB];
+    const int64_t i = ct * 32 + col;
+    {
+        float yv[DIM], ys2 = 0.0f;
 #pragma unroll
-            for (int k = 0; k < MDGMI_MAX_BITS; k++) {
-                if (k < m) {
-                    float S0k, S1k;
-                    full_sums(p0, p1, k, S0k, S1k);
-                    smin = fminf(smin, fminf(S0k, S1k));
-                }
-            }
-            // a class of some sample of this column lies too far for the
-            // common offset (or y is not finite): second pass for the column
-            // (columns past n, at y = 0, do not count)
-            if (__ballot(i < n && !(smin >= ex2(kFarLog2))) != 0ull) {
-                llr_far_pass<DIM, G, MAXHI, S>(A, ys, n, i, M, m, ntiles, s, X32, llr, p0, p1);
-                continue;
-            }
-            constexpr int NJ = (MDGMI_MAX_BITS + 1) / 2;
-            float lam[NJ];
-            bool near0 = false;
-#pragma unroll
-            for (int j = 0; j < NJ; j++) {
-                lam[j] = 0.0f;
-                if (2 * j < m) {  // uniform
-                    const int ke = 2 * j, ko = ke + 1 < MDGMI_MAX_BITS ? ke + 1 : ke;
-                    float S0e, S1e, S0o = 1.0f, S1o = 1.0f;
-                    if (ke == 2) {
-                        S0e = S0t;
-                        S1e = S1t;
-                    } else {
-                        full_sums(p0, p1, ke, S0e, S1e);
-                    }
-                    if (ko < m) full_sums(p0, p1, ko, S0o, S1o);
-                    const int k = ke + h;
-                    const float s0 = h ? S0o : S0e, s1 = h ? S1o : S1e;
-                    lam[j] = log2_ratio_fast(s1, s0);
-                    if (k < m) near0 = near0 || fabsf(lam[j]) < guard;
-                }
-            }
-            // an LLR near zero at a large s (either half's bits): the whole
-            // sample is recomputed on the per-class path by lane half 0
-            const Halves hz = halves(near0 ? 1.0f : 0.0f);
-            const bool redo = hz.lo + hz.hi > 0.0f;
-            if (i >= n) continue;
-            if (!redo) {
-#pragma unroll
-                for (int j = 0; j < NJ; j++) {
-                    const int k = 2 * j + h;
-                    if (k < m) llr[i * m + k] = lam[j] * (float)kLn2;
-                }
-            } else if (h == 0) {
-                float yc[DIM], ls0[MDGMI_MAX_BITS], ls1[MDGMI_MAX_BITS], ltot, ti;
-#pragma unroll
-                for (int d = 0; d < DIM; d++) yc[d] = ys[i * DIM + d];
-                exact_classes_f32<DIM>(yc, X32, M, m, s, -1, ls0, ls1, ltot, ti);
-#pragma unroll
-                for (int k = 0; k < MDGMI_MAX_BITS; k++)
-                    if (k < m) llr[i * m + k] = (ls1[k] - ls0[k]) * (float)kLn2;
-            }
-            continue;
+        for (int d = 0; d < DIM; d++) {
+            yv[d] = i < n ? ys[i * DIM + d] : 0.0f;
+            ys2 = fmaf(yv[d], yv[d], ys2);
         }
-        // a sent row outside [0, M) gives a NaN cost instead of a stray read
-        const uint32_t row = i < n ? txs[i] : 0u;
-        const bool row_ok = row < (uint32_t)M;
-        const uint32_t lw = labels[row_ok ? row : 0u];
-        const uint32_t slot = lw & kLabelMask;
-        const bool twin = HD && (lw & kTwinBit) != 0u;  // a lower label shares the sent point
-        // u of the sent point by the matrix cores themselves: one more MFMA
-        // whose row r is the sent point of sample r puts u_i(y) on the
-        // diagonal, bit-identical to the value inside the class sums, so the
-        // MI cost log2 sum_j 2^(u_j - u_i) carries no recomputation error.
-        // Diagonal element r sits in lane half (r >> 2) & 1, register
-        // ((r >> 3) << 2) | (r & 3).
-        half8 ad[NB];
-        load_a_at<NB>(A + (int)(slot >> 5) * TS + h * 32 + (int)(slot & 31), ad);
-        const f32x16 ud = tile_mfma<NB, S>(ad, bop[c]);
-        const int q = ((col >> 3) << 2) | (col & 3);
-        float dv = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; r++) dv = (r == q) ? ud[r] : dv;
-        const Halves d = halves(dv);
-        const float ui = ((col >> 2) & 1) ? d.hi : d.lo;
-        // this half's class sums of its bit pair j (bit 2j + h)
-        auto own_sums = [&](int j, float& s0, float& s1) {
-            const int ke = 2 * j, ko = ke + 1 < MDGMI_MAX_BITS ? ke + 1 : ke;
-            float S0e, S1e, S0o = 1.0f, S1o = 1.0f;
-            if (ke == 2) {
-                S0e = S0t;
-                S1e = S1t;
-            } else {
-                full_sums(p0, p1, ke, S0e, S1e);
-            }
-            if (ko < m) full_sums(p0, p1, ko, S0o, S1o);
-            s0 = h ? S0o : S0e;
-            s1 = h ? S1o : S1e;
-        };
-        // GMI cost of this half's bits, sum_k log2(T / S_sent,k), as one
-        // logarithm of the product of S_sent,k / T (cost_from_product)
-        float cg = 0.0f, be = 0.0f, prod = 1.0f;
-        const float rT = __builtin_amdgcn_rcpf(tot);
-#pragma unroll
-        for (int j = 0; j < (MDGMI_MAX_BITS + 1) / 2; j++) {
-            if (2 * j < m) {  // uniform
-                float s0, s1;
-                own_sums(j, s0, s1);
-                const int k = 2 * j + h;
-                if (k < m) {
-                    const bool bk = (slot >> k) & 1;
-                    prod *= (bk ? s1 : s0) * rT;
-                    if (HD) be += (s1 > s0) != bk ? 1.0f : 0.0f;  // bitwise MAP decision
-                }
-            }
-        }
-        const bool fast = prod >= 0x1p-120f;
-        if (__ballot(!fast) == 0ull) {
-            cost_from_product(prod, cg);
-        } else {
-            // some sample of the wave has a cost beyond 120 bits or a
-            // non-finite sum: bit by bit, log2(1 + S_other / S_sent)
-            asm volatile("" ::: "memory");  // keeps the rare path a real branch
-#pragma unroll
-            for (int j = 0; j < (MDGMI_MAX_BITS + 1) / 2; j++) {
-                if (2 * j < m) {
-                    float s0, s1;
-                    own_sums(j, s0, s1);
-                    const int k = 2 * j + h;
-                    if (k < m) cg += bit_cost_sum2(s0 + s1, ((slot >> k) & 1) ? s1 : s0);
-                }
-            }
-        }
-        cg = half_sum(cg);
-        float sym = 0.0f;
-        if (HD) {
-            be = half_sum(be);
-            const Halves um = halves(umax[c]);
-            // another point strictly nearer, or the sent point's coordinates
-            // shared with a lower label (ties go to the lowest label)
-            sym = fmaxf(um.lo, um.hi) > ui || twin ? 1.0f : 0.0f;
-        }
-        if (h != 0 || i >= n) continue;
-        float cm;
-        if (ui >= kFarLog2) {
-            cm = mi_cost2(tot, ui);
-        } else {
-            // the sent point itself is far from y (or y is not finite)
-            float yc[DIM], ls0[MDGMI_MAX_BITS], ls1[MDGMI_MAX_BITS], ltot, ti = 0.0f, tmin = 0.0f;
-#pragma unroll
-            for (int dd = 0; dd < DIM; dd++) yc[dd] = ys[i * DIM + dd];
-            exact_classes_f32<DIM>(yc, X32, M, m, s, (int)slot, ls0, ls1, ltot, ti, HD ? &tmin : nullptr);
-            cg = 0.0f;
-            be = 0.0f;
-            // the split factors may be out of range here: decide the symbol
-            // from the FP32 distances as well
-            if (HD) sym = tmin < ti || twin ? 1.0f : 0.0f;
-#pragma unroll
-            for (int k = 0; k < MDGMI_MAX_BITS; k++) {
-                if (k < m) {
-                    const bool bk = (slot >> k) & 1;
-                    cg += bit_cost2(bk ? ls0[k] - ls1[k] : ls1[k] - ls0[k]);
-                    if (HD) be += (ls1[k] > ls0[k]) != bk ? 1.0f : 0.0f;  // from the exact logarithms
-                }
-            }
-            cm = ltot + ti;
-        }
-        if (!row_ok) cg = cm = NAN;
-        acc.add(cg, cm);
-        if (HD) {
-            const bool finite = cg == cg && cm == cm && ui == ui;
-            hd->be += finite ? (double)be : (double)m;
-            hd->se += finite ? (double)sym : 1.0;
-        }
+        make_b<DIM, S>(yv, fmaf(-s, ys2, kBias), h, bop[0]);
     }
+    float bank[1][16], umax[1] = {0.0f};
+    HiAcc<8, MAXHI> hi[1];
+    tile_loop<DIM, 1, 8, false, MAXHI, HD, S>(A + wave * 8 * NB * 64, 8, h, col, bop, bank, hi, umax);
+    float* own = sums + wave * kSplitSums * 64 + lane;
+#pragma unroll
+    for (int r = 0; r < 16; r++) own[r * 64] = bank[0][r];
+#pragma unroll
+    for (int l = 0; l < 3; l++) {
+        own[(16 + l) * 64] = hi[0].R0[l];
+        own[(19 + l) * 64] = hi[0].R1[l];
+    }
+    own[22 * 64] = hi[0].R0[3];  // group 0 of one: its total
+    if (HD) own[23 * 64] = umax[0];
+    __syncthreads();
+    // sums over the groups, in order, in the first wave's rows
+    for (int e = threadIdx.x; e < 22 * 64; e += waves * 64) {
+        float v = sums[e];
+        for (int w = 1; w < waves; w++) v += sums[w * kSplitSums * 64 + e];
+        sums[e] = v;
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) bank[0][r] = own[r * 64];
+#pragma unroll
+        for (int l = 0; l < 3; l++) {
+            hi[0].R0[l] = own[(16 + l) * 64];
+            hi[0].R1[l] = own[(19 + l) * 64];
+        }
+#pragma unroll
+        for (int l = 3; l < MAXHI; l++) hi[0].R0[l] = hi[0].R1[l] = 0.0f;
+        for (int w = 0; w < waves; w++) {
+            const float T = own[(w * kSplitSums + 22) * 64];
+            if (HD) umax[0] = fmaxf(umax[0], own[(w * kSplitSums + 23) * 64]);
+#pragma unroll
+            for (int l = 3; l < MAXHI; l++) {
+                if ((w >> (l - 3)) & 1)
+                    hi[0].R1[l] += T;
+                else
+                    hi[0].R0[l] += T;
+            }
+        }
+        mfma_finish<DIM, 8, MODE, S>(A, ys, txs, n, i, M, m, ntiles, s, X32, labels, llr, acc, hd, guard, bop[0],
+                                     bank[0], hi[0], umax[0]);
+    }
+    __syncthreads();  // before the next column's sums
 }
 
 // ---- max-log metrics --------------------------------------------------

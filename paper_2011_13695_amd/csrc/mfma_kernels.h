@@ -15,6 +15,7 @@ struct MfmaShape {
     enum Kind { kVariant = 0, kFixed = 1, kWide = 2 } kind;
     int var;
     bool lds;
+    bool forced;   // var was asked for by mdgmi_set_tuning: no other shape in its place
 };
 
 // Builds the per-SNR operand images, then runs the demapper kernel.
@@ -82,6 +83,65 @@ __global__ __launch_bounds__(WAVES * 64) void k_mfma(
     if (MODE == kModeHd) block_reduce_store_hd(acc, hd, dst);
 }
 
+
+// The points of a column tile split over the waves of a block
+// (mfma_split_coltile), the image read from L2.
+template <int DIM, int MODE>
+__global__ __launch_bounds__(1024) void k_mfma_split(
+    const float* __restrict__ y, const uint32_t* __restrict__ tx, const uint4* __restrict__ img,
+    const float* __restrict__ X32, const uint32_t* __restrict__ labels, int64_t n, int M, int m, int ntiles, SnrArgs sa,
+    float max_n2, float* __restrict__ llr, double* __restrict__ part) {
+    constexpr int NB = Blk<DIM>::value;
+    extern __shared__ uint4 lds_img[];
+    const int q_snr = blockIdx.y;
+    const float s = sa.s32[q_snr];
+    const int64_t snr = sa.snr0 + q_snr;
+    const uint4* __restrict__ A = img + (size_t)q_snr * ntiles * NB * 64;
+    const float* ys = y + snr * n * DIM;
+    const uint32_t* txs = mode_is_llr(MODE) ? nullptr : tx + snr * n;
+    CostAcc acc;
+    HdAcc hd;
+    const float guard = mode_is_llr(MODE) ? llr_guard(s, max_n2) : 0.0f;
+    const int64_t ncoltiles = (n + 31) / 32;
+    for (int64_t ct = blockIdx.x; ct < ncoltiles; ct += gridDim.x)
+        mfma_split_coltile<DIM, MODE>(A, ys, txs, n, ct, M, m, ntiles, s, X32, labels, llr, acc, &hd, guard,
+                                      (float*)lds_img);
+    double* dst = part + ((int64_t)q_snr * gridDim.x + blockIdx.x) * (MODE == kModeHd ? kNPartHd : kNPart);
+    if (MODE == kModeGmi) block_reduce_store(acc, dst);
+    if (MODE == kModeHd) block_reduce_store_hd(acc, hd, dst);
+}
+
+// Column tiles of a launch (over its SNR points) up to which the points are
+// split: two per CU. 8-D M = 2048, two points of 1500 samples (94 column tiles): the
+// call 24 us with a wave per tile, 19 us split (48 us with sixteen tiles per block).
+inline bool split_points(int mode, int ntiles, int64_t n, int n_snr) {
+    return !mode_is_ml(mode) && ntiles >= 16 && (n + 31) / 32 * n_snr <= (int64_t)device_cu_count() * 2;
+}
+
+template <int DIM>
+hipError_t launch_split(int mode, const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n,
+                        const SnrArgs& sa, float* llr, double* part, const uint4* img, int ntiles, int blocks,
+                        hipStream_t st) {
+    const dim3 grid(blocks, sa.n_snr), block(ntiles / 8 * 64);
+    const size_t lds = (size_t)(ntiles / 8) * kSplitSums * 64 * sizeof(float);
+#define MDGMI_SPLIT(MD)                                                                                             \
+    case MD: {                                                                                                      \
+        hipError_t e = hipFuncSetAttribute((const void*)k_mfma_split<DIM, MD>,                                      \
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
+        if (e != hipSuccess) return e;                                                                              \
+        hipLaunchKernelGGL((k_mfma_split<DIM, MD>), grid, block, lds, st, y, tx, img, f->d_X32,                     \
+                           MD == kModeHd ? f->d_labels_hd : f->d_labels, n, f->M, f->m, ntiles, sa,                 \
+                           (float)f->max_norm2, llr, part);                                                         \
+        return hipGetLastError();                                                                                   \
+    }
+    switch (mode) {
+        MDGMI_SPLIT(kModeLlr)
+        MDGMI_SPLIT(kModeHd)
+        default:
+            MDGMI_SPLIT(kModeGmi)
+    }
+#undef MDGMI_SPLIT
+}
 
 template <int DIM, int NCOL, int WAVES, int G, bool LDS, int MODE, int S = kSplitF16>
 hipError_t launch_vm(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
@@ -220,6 +280,10 @@ hipError_t mfma_run(const mdgmi_format* f, const float* y, const uint32_t* tx, i
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int b = cfg.blocks_per_snr;
+    if constexpr (S == kSplitF16) {
+        if (!shape.forced && split_points(mode, ntiles, n, sa.n_snr))
+            return launch_split<DIM>(mode, f, y, tx, n, sa, llr, part, img, ntiles, b, st);
+    }
     if constexpr (DIM > 1) {
         if (shape.kind == MfmaShape::kWide)
             return launch_wide_l2<DIM, S>(mode, f, y, tx, n, sa, llr, part, img, ntiles, b, st);
