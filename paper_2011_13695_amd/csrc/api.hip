@@ -82,7 +82,7 @@ int part_stride(int mode) { return mode == kModeHd ? kNPartHd : kNPart; }
 GmiPlan plan_gmi(const mdgmi_format* f, int64_t n, int n_snr, int path, int mode) {
     GmiPlan p{};
     p.path = path;
-    const int per_launch = std::min(n_snr, kMaxSnrPerLaunch);
+    const int per_launch = std::min(n_snr, kMaxSnrPerLaunch);  // (room for any subset of the points)
     if (path == MDGMI_PATH_F64) {
         p.cfg = f64_cfg(f, n, n_snr, mode);
         p.image_bytes = 0;
@@ -181,8 +181,9 @@ int run_gmi(const mdgmi_format* fmt, const void* y, const uint32_t* tx_idx, int6
     hipStream_t st = (hipStream_t)stream;
     double* part = (double*)ws;
     void* image = (char*)ws + align_up(pl.part_bytes);
-    for (int q0 = 0; q0 < n_snr; q0 += kMaxSnrPerLaunch) {
-        const int cnt = std::min(kMaxSnrPerLaunch, n_snr - q0);
+    const int per_launch = snr_per_launch(n_snr);
+    for (int q0 = 0; q0 < n_snr; q0 += per_launch) {
+        const int cnt = std::min(per_launch, n_snr - q0);
         SnrArgs sa = snr_args(sigma2_host, q0, cnt);
         double* pq = part + (size_t)q0 * pl.cfg.blocks_per_snr * part_stride(mode);
         if (launch_exact(fmt, p, y, tx_idx, n, sa, mode, nullptr, pq, image, pl.cfg, st) != hipSuccess)

@@ -378,7 +378,7 @@ hipError_t launch_f64_d(const mdgmi_format* f, const double* y, const uint32_t* 
 LaunchCfg f64_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode) {
     (void)f;
     const int64_t want = (n + kF64Threads - 1) / kF64Threads;
-    const int snr_in_launch = n_snr < kMaxSnrPerLaunch ? n_snr : kMaxSnrPerLaunch;
+    const int snr_in_launch = snr_per_launch(n_snr);
     const int64_t cap = std::max<int64_t>(1, (int64_t)device_cu_count() * (mode_is_llr(mode) ? 12 : 6) / snr_in_launch);
     const int64_t strides = (want + cap - 1) / cap;
     LaunchCfg c;

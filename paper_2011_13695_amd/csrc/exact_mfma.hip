@@ -71,7 +71,7 @@ LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int split, int 
     const int by_lds = lds ? std::max(1, (int)((160 * 1024) / (img + 2048))) : 8;
     const int by_waves = std::max(1, 16 / v.waves);
     const int64_t total = (int64_t)device_cu_count() * std::min(by_lds, by_waves);
-    const int snr_in_launch = n_snr < kMaxSnrPerLaunch ? n_snr : kMaxSnrPerLaunch;
+    const int snr_in_launch = snr_per_launch(n_snr);
     int64_t per = std::max<int64_t>(1, total / snr_in_launch);
     // a short call takes a block per column tile as far as there are CUs: the
     // tiles go to the blocks in turn, a wave or two of each has work, and a SIMD
@@ -104,7 +104,7 @@ size_t mfma_image_bytes(const mdgmi_format* f, int n_snr, int split) {
 LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split) {
     const int64_t total = n * (int64_t)n_snr;
     if (use_small(f, split, total)) {
-        LaunchCfg c = small_cfg(f, n, n_snr);
+        LaunchCfg c = small_cfg(f, n, n_snr, mode);
         c.variant = kSmallVariant;
         return c;
     }
@@ -117,16 +117,24 @@ LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int sp
 }
 
 int64_t mfma_blocks_bound(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split) {
-    // per shape, the blocks of a call over k of the n_snr points: the blocks
-    // per point depend on k only up to kMaxSnrPerLaunch points per launch,
-    // beyond which k times them grows with k, so k = 1..32 and k = n_snr
+    // per shape, the blocks of a call over k of the n_snr points: k times the
+    // blocks per point of a launch's snr_per_launch(k) points, for k up to
+    // twice a launch's limit and k = n_snr; for the k between, at most a
+    // launch's blocks times the launches
     int64_t b = (int64_t)n_snr * mfma_cfg(f, n, n_snr, mode, split).blocks_per_snr;
-    for (int k = 1; k <= n_snr; k = (k < kMaxSnrPerLaunch || k == n_snr) ? k + 1 : n_snr) {
-        if (split == kSplitF16 && small_shape_fits(f))
-            b = std::max<int64_t>(b, (int64_t)k * small_cfg(f, n, k).blocks_per_snr);
-        for (int v = -1; v < kNumVariants; v++)
-            b = std::max<int64_t>(b, (int64_t)k * shape_cfg(f, n, k, split, v).blocks_per_snr);
-    }
+    const int most = std::min(n_snr, 2 * kMaxSnrPerLaunch);
+    const int64_t launches = (n_snr + kMaxSnrPerLaunch - 1) / kMaxSnrPerLaunch;
+    auto take = [&](auto cfg) {
+        int64_t per_launch = 0;
+        for (int k = 1; k <= most; k++) {
+            const int64_t blocks = (int64_t)k * cfg(k).blocks_per_snr;
+            b = std::max(b, blocks);
+            if (k <= kMaxSnrPerLaunch) per_launch = std::max(per_launch, blocks);
+        }
+        if (n_snr > most) b = std::max({b, launches * per_launch, (int64_t)n_snr * cfg(n_snr).blocks_per_snr});
+    };
+    if (split == kSplitF16 && small_shape_fits(f)) take([&](int k) { return small_cfg(f, n, k, mode); });
+    for (int v = -1; v < kNumVariants; v++) take([&](int k) { return shape_cfg(f, n, k, split, v); });
     return b;
 }
 

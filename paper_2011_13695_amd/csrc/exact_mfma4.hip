@@ -1,6 +1,7 @@
 // Per-SNR kernels of the per-sample 4x4-block MFMA demapper for small
 // constellations (the arithmetic is in small_core.h).
 #include <algorithm>
+#include <atomic>
 
 #include "small_core.h"
 
@@ -110,6 +111,33 @@ hipError_t launch_small_d(const mdgmi_format* f, const float* y, const uint32_t*
     }
 }
 
+template <int DIM, int NG>
+const void* small_kernel_t(int mode) {
+    switch (mode) {
+        case kModeLlr: return (const void*)k_small<DIM, NG, kModeLlr>;
+        case kModeHd: return (const void*)k_small<DIM, NG, kModeHd>;
+        case kModeMlLlr: return (const void*)k_small<DIM, NG, kModeMlLlr>;
+        case kModeMlGmi: return (const void*)k_small<DIM, NG, kModeMlGmi>;
+        default: return (const void*)k_small<DIM, NG, kModeGmi>;
+    }
+}
+
+template <int DIM>
+const void* small_kernel_d(int M, int mode) {
+    switch (M) {
+        case 4: return small_kernel_t<DIM, 1>(mode);
+        case 8: return small_kernel_t<DIM, 2>(mode);
+        case 16: return small_kernel_t<DIM, 4>(mode);
+        case 32: return small_kernel_t<DIM, 8>(mode);
+        case 64: return small_kernel_t<DIM, 16>(mode);
+        case 128: return small_kernel_t<DIM, 32>(mode);
+        case 256: return small_kernel_t<DIM, 64>(mode);
+        default:
+            if constexpr (DIM < 8) return small_kernel_t<DIM, 128>(mode);
+            return nullptr;
+    }
+}
+
 }  // namespace
 
 bool small_shape_fits(const mdgmi_format* f) {
@@ -123,13 +151,42 @@ size_t small_image_bytes(const mdgmi_format* f, int n_snr) {
     return (size_t)n_snr * f->M * nk * sizeof(uint2);
 }
 
-LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr) {
-    (void)f;
+// Blocks of (dim, M, mode)'s kernel that a CU holds, from its registers; asked
+// of the runtime once. 0 if the format is not served.
+static int small_blocks_per_cu(int dim, int M, int mode) {
+    static std::atomic<int> cache[4][8][5];
+    int lm = 0;
+    while ((4 << lm) < M) lm++;
+    const int ld = dim == 1 ? 0 : dim == 2 ? 1 : dim == 4 ? 2 : 3;
+    if (lm > 7 || mode < 0 || mode > 4) return 0;
+    std::atomic<int>& c = cache[ld][lm][mode];
+    int v = c.load(std::memory_order_relaxed);
+    if (v == 0) {
+        const void* k = nullptr;
+        switch (dim) {
+            case 1: k = small_kernel_d<1>(M, mode); break;
+            case 2: k = small_kernel_d<2>(M, mode); break;
+            case 4: k = small_kernel_d<4>(M, mode); break;
+            default: k = small_kernel_d<8>(M, mode); break;
+        }
+        if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, kSmallThreads, 0) != hipSuccess || v < 1) v = 4;
+        v = std::min(v, 8);
+        c.store(v, std::memory_order_relaxed);
+    }
+    return v;
+}
+
+// One resident round of blocks over the launch's SNR points, as many per CU as
+// the kernel's registers allow (3 to 8). Four per CU for every format left the
+// light ones waiting on their loads and dependent operations: 64-QAM LLRs of
+// 2^22 samples 58 us, now @@OCC1@@; 16-QAM hard decisions, 41 points of 131071
+// samples, 60 us (as 32 + 9 points), now @@OCC2@@. Calls of very many points keep
+// four, and with it the partial sums they had room for.
+LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode) {
     const int64_t batches = (n + 63) / 64;
     const int64_t want = (batches + kSmallThreads / 64 - 1) / (kSmallThreads / 64);
-    // about four blocks per CU over the launch's SNR points
-    const int snr_in_launch = n_snr < kMaxSnrPerLaunch ? n_snr : kMaxSnrPerLaunch;
-    int64_t per = std::max<int64_t>(1, (int64_t)device_cu_count() * 4 / snr_in_launch);
+    const int per_cu = n_snr <= 8 * kMaxSnrPerLaunch ? small_blocks_per_cu(f->dim, f->M, mode) : 4;
+    int64_t per = std::max<int64_t>(1, (int64_t)device_cu_count() * per_cu / snr_per_launch(n_snr));
     per = std::min<int64_t>(per, std::max<int64_t>(1, want));
     LaunchCfg c;
     c.threads = kSmallThreads;

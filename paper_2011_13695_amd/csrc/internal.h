@@ -47,6 +47,13 @@ __host__ __device__ constexpr bool mode_is_ml(int mode) { return mode == kModeMl
 // what the final reduction writes: GMI/MI, + hard decisions, or GMI only
 constexpr int kReduceGmi = 0, kReduceHd = 1, kReduceMl = 2;
 constexpr int kMaxSnrPerLaunch = 32;
+// SNR points per launch of a call over n_snr: as few launches as the limit
+// allows, of equal size (41 points as 32 + 9 left the second launch a quarter of
+// the chip's blocks: each launch's blocks per point follow from its points).
+inline int snr_per_launch(int n_snr) {
+    const int launches = (n_snr + kMaxSnrPerLaunch - 1) / kMaxSnrPerLaunch;
+    return (n_snr + launches - 1) / launches;
+}
 // Exponents are taken relative to a fixed offset: e_j = 2^(kBias - t_j) with
 // t_j = ||y - x_j||^2 / (2 sigma2) * log2(e) >= 0, so no term can overflow
 // (M * 2^kBias < 2^128) and any class whose nearest point lies within
@@ -106,7 +113,7 @@ bool small_shape_fits(const mdgmi_format* f);
 // samples (tuning table, override): the ragged batch's choice
 bool prefers_small(const mdgmi_format* f);
 size_t small_image_bytes(const mdgmi_format* f, int n_snr);
-LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr);
+LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode);
 hipError_t launch_small(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
                         int mode, float* llr, double* part, void* image, LaunchCfg cfg, hipStream_t st);
 
