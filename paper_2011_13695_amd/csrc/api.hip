@@ -82,17 +82,22 @@ int part_stride(int mode) { return mode == kModeHd ? kNPartHd : kNPart; }
 GmiPlan plan_gmi(const mdgmi_format* f, int64_t n, int n_snr, int path, int mode) {
     GmiPlan p{};
     p.path = path;
-    const int per_launch = std::min(n_snr, kMaxSnrPerLaunch);  // (room for any subset of the points)
+    // images of one launch, with room for any subset of the points
+    const int images = std::min(n_snr, kMaxSnrPerLaunch);
+    p.per_launch = snr_per_launch(n_snr);
     if (path == MDGMI_PATH_F64) {
         p.cfg = f64_cfg(f, n, n_snr, mode);
         p.image_bytes = 0;
     } else if (path == MDGMI_PATH_F32_DIRECT) {
         p.cfg = direct_cfg(f, n);
-        p.image_bytes = direct_image_bytes(f, per_launch);
+        p.image_bytes = direct_image_bytes(f, images);
     } else {
         const int split = path == MDGMI_PATH_F32_MFMA_BF16SPLIT ? 1 : 0;
         p.cfg = mfma_cfg(f, n, n_snr, mode, split);
-        p.image_bytes = mfma_image_bytes(f, per_launch, split);
+        p.image_bytes = mfma_image_bytes(f, images, split);
+        if (split == 0 && small_shape_fits(f))
+            p.image_bytes = std::max(p.image_bytes, small_image_bytes(f, std::min(n_snr, kMaxSnrSmall)));
+        if (p.cfg.variant == kSmallVariant) p.per_launch = snr_per_launch(n_snr, kMaxSnrSmall);
     }
     int64_t blocks = (int64_t)n_snr * p.cfg.blocks_per_snr;
     // FP64 launches take fewer blocks per point the more points share them,
@@ -117,7 +122,7 @@ SnrArgs snr_args(const double* sigma2, int q0, int cnt) {
         const double s2 = sigma2[q0 + q];
         sa.s64[q] = s_of(s2);
         sa.s32[q] = (float)sa.s64[q];
-        sa.inv2s2[q] = 1.0 / (2.0 * s2);
+        if (q < kMaxSnrPerLaunch) sa.inv2s2[q] = 1.0 / (2.0 * s2);
     }
     return sa;
 }
@@ -181,9 +186,8 @@ int run_gmi(const mdgmi_format* fmt, const void* y, const uint32_t* tx_idx, int6
     hipStream_t st = (hipStream_t)stream;
     double* part = (double*)ws;
     void* image = (char*)ws + align_up(pl.part_bytes);
-    const int per_launch = snr_per_launch(n_snr);
-    for (int q0 = 0; q0 < n_snr; q0 += per_launch) {
-        const int cnt = std::min(per_launch, n_snr - q0);
+    for (int q0 = 0; q0 < n_snr; q0 += pl.per_launch) {
+        const int cnt = std::min(pl.per_launch, n_snr - q0);
         SnrArgs sa = snr_args(sigma2_host, q0, cnt);
         double* pq = part + (size_t)q0 * pl.cfg.blocks_per_snr * part_stride(mode);
         if (launch_exact(fmt, p, y, tx_idx, n, sa, mode, nullptr, pq, image, pl.cfg, st) != hipSuccess)

@@ -118,23 +118,25 @@ LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int sp
 
 int64_t mfma_blocks_bound(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split) {
     // per shape, the blocks of a call over k of the n_snr points: k times the
-    // blocks per point of a launch's snr_per_launch(k) points, for k up to
-    // twice a launch's limit and k = n_snr; for the k between, at most a
-    // launch's blocks times the launches
+    // blocks per point of a launch's points, for k up to twice a launch's limit
+    // and k = n_snr; for the k between, at most a launch's blocks times the
+    // launches
     int64_t b = (int64_t)n_snr * mfma_cfg(f, n, n_snr, mode, split).blocks_per_snr;
-    const int most = std::min(n_snr, 2 * kMaxSnrPerLaunch);
-    const int64_t launches = (n_snr + kMaxSnrPerLaunch - 1) / kMaxSnrPerLaunch;
-    auto take = [&](auto cfg) {
+    auto take = [&](int limit, auto cfg) {
+        const int most = std::min(n_snr, 2 * limit);
         int64_t per_launch = 0;
         for (int k = 1; k <= most; k++) {
             const int64_t blocks = (int64_t)k * cfg(k).blocks_per_snr;
             b = std::max(b, blocks);
-            if (k <= kMaxSnrPerLaunch) per_launch = std::max(per_launch, blocks);
+            if (k <= limit) per_launch = std::max(per_launch, blocks);
         }
-        if (n_snr > most) b = std::max({b, launches * per_launch, (int64_t)n_snr * cfg(n_snr).blocks_per_snr});
+        if (n_snr > most)
+            b = std::max({b, (n_snr + limit - 1) / limit * per_launch, (int64_t)n_snr * cfg(n_snr).blocks_per_snr});
     };
-    if (split == kSplitF16 && small_shape_fits(f)) take([&](int k) { return small_cfg(f, n, k, mode); });
-    for (int v = -1; v < kNumVariants; v++) take([&](int k) { return shape_cfg(f, n, k, split, v); });
+    if (split == kSplitF16 && small_shape_fits(f))
+        take(kMaxSnrSmall, [&](int k) { return small_cfg(f, n, k, mode); });
+    for (int v = -1; v < kNumVariants; v++)
+        take(kMaxSnrPerLaunch, [&](int k) { return shape_cfg(f, n, k, split, v); });
     return b;
 }
 

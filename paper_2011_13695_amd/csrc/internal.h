@@ -47,11 +47,15 @@ __host__ __device__ constexpr bool mode_is_ml(int mode) { return mode == kModeMl
 // what the final reduction writes: GMI/MI, + hard decisions, or GMI only
 constexpr int kReduceGmi = 0, kReduceHd = 1, kReduceMl = 2;
 constexpr int kMaxSnrPerLaunch = 32;
+// ... and of the per-sample 4x4 shape: its images are small, and with a quarter of
+// a round of blocks lost at each launch's end, one launch of 41 points of 131071
+// 16-QAM samples took 42.5 us where two of 21 and 20 took 52
+constexpr int kMaxSnrSmall = 64;
 // SNR points per launch of a call over n_snr: as few launches as the limit
 // allows, of equal size (41 points as 32 + 9 left the second launch a quarter of
 // the chip's blocks: each launch's blocks per point follow from its points).
-inline int snr_per_launch(int n_snr) {
-    const int launches = (n_snr + kMaxSnrPerLaunch - 1) / kMaxSnrPerLaunch;
+inline int snr_per_launch(int n_snr, int most = kMaxSnrPerLaunch) {
+    const int launches = (n_snr + most - 1) / most;
     return (n_snr + launches - 1) / launches;
 }
 // Exponents are taken relative to a fixed offset: e_j = 2^(kBias - t_j) with
@@ -79,9 +83,9 @@ constexpr double kLn2 = 0.6931471805599453;
 struct SnrArgs {
     int n_snr;                 // SNR points in this launch
     int snr0;                  // index of the first one in the caller's arrays
-    float s32[kMaxSnrPerLaunch];   // s = log2(e) / (2 sigma2)
-    double s64[kMaxSnrPerLaunch];
-    double inv2s2[kMaxSnrPerLaunch];  // 1 / (2 sigma2)
+    float s32[kMaxSnrSmall];   // s = log2(e) / (2 sigma2)
+    double s64[kMaxSnrSmall];
+    double inv2s2[kMaxSnrPerLaunch];  // 1 / (2 sigma2), for the FP64 launches
 };
 
 struct LaunchCfg {
@@ -143,6 +147,7 @@ struct GmiPlan {
     int path;
     LaunchCfg cfg;
     size_t part_bytes, image_bytes, total;
+    int per_launch;            // SNR points of each launch (the last may have fewer)
 };
 GmiPlan plan_gmi(const mdgmi_format* f, int64_t n, int n_snr, int path, int mode = kModeGmi);
 SnrArgs snr_args(const double* sigma2, int q0, int cnt);
