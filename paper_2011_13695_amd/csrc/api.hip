@@ -166,9 +166,12 @@ int gmi_workspace_size(const mdgmi_format* fmt, int64_t n, int32_t n_snr, int32_
 }
 
 // One pass over n samples at n_snr noise levels: per-block partial sums
-// (launches of at most kMaxSnrPerLaunch SNR points), then the FP64 reduce.
+// (launches of at most kMaxSnrPerLaunch SNR points), then the FP64 reduce. n_plan:
+// the SNR points of the caller's call these are part of, if more: the launches
+// are then those of that call, and so are the bits of the results.
 int run_gmi(const mdgmi_format* fmt, const void* y, const uint32_t* tx_idx, int64_t n, const double* sigma2_host,
-            int32_t n_snr, int32_t path, int mode, double* out, void* ws, size_t ws_bytes, void* stream) {
+            int32_t n_snr, int32_t path, int mode, double* out, void* ws, size_t ws_bytes, void* stream,
+            int32_t n_plan = 0) {
     if (!fmt || !y || !tx_idx || !sigma2_host || !out) return MDGMI_E_NULL;
     if (n < 1 || n_snr < 1) return MDGMI_E_SHAPE;
     double max_s = 0.0;
@@ -177,9 +180,10 @@ int run_gmi(const mdgmi_format* fmt, const void* y, const uint32_t* tx_idx, int6
         max_s = std::max(max_s, s_of(sigma2_host[q]));
     }
     int p = 0;
-    int rc = resolve_path(fmt, path, max_s, &p, n * (int64_t)n_snr);
+    n_plan = std::max(n_plan, n_snr);
+    int rc = resolve_path(fmt, path, max_s, &p, n * (int64_t)n_plan);
     if (rc != MDGMI_OK) return rc;
-    GmiPlan pl = plan_gmi(fmt, n, n_snr, p, mode);
+    GmiPlan pl = plan_gmi(fmt, n, n_plan, p, mode);
     if (!ws || ws_bytes < pl.total) return MDGMI_E_WORKSPACE;
     rc = check_device(fmt);
     if (rc != MDGMI_OK) return rc;
@@ -224,10 +228,10 @@ int run_llr(const mdgmi_format* fmt, const void* y, int64_t n, double sigma2, vo
 
 int gmi_with_workspace(const mdgmi_format* fmt, const void* y, const uint32_t* tx_idx, int64_t n,
                        const double* sigma2_host, int32_t n_snr, int32_t path, double* out, void* ws, size_t ws_bytes,
-                       void* stream) {
+                       void* stream, int32_t n_plan) {
     if (path == MDGMI_PATH_LEARNED_BF16)
         return learned_gmi(fmt, (const float*)y, tx_idx, n, sigma2_host, n_snr, out, ws, ws_bytes, stream);
-    return run_gmi(fmt, y, tx_idx, n, sigma2_host, n_snr, path, kModeGmi, out, ws, ws_bytes, stream);
+    return run_gmi(fmt, y, tx_idx, n, sigma2_host, n_snr, path, kModeGmi, out, ws, ws_bytes, stream, n_plan);
 }
 }  // namespace mdgmi
 

@@ -101,6 +101,14 @@ size_t mfma_image_bytes(const mdgmi_format* f, int n_snr, int split) {
     return big;
 }
 
+// Column tiles of a launch (over its SNR points) up to which the points are
+// split: two per CU. 8-D M = 2048, two points of 1500 samples (94 column tiles): the
+// call 24 us with a wave per tile, 19 us split (48 us with sixteen tiles per block).
+static bool split_points(const mdgmi_format* f, int mode, int64_t n, int n_snr) {
+    return !mode_is_ml(mode) && (f->M + 31) / 32 >= 16 &&
+           (n + 31) / 32 * snr_per_launch(n_snr) <= (int64_t)device_cu_count() * 2;
+}
+
 LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split) {
     const int64_t total = n * (int64_t)n_snr;
     if (use_small(f, split, total)) {
@@ -113,7 +121,10 @@ LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int sp
     // 1-column, 16-wave shape only (LDS image if it fits)
     const bool fixed = mode == kModeHd || mode_is_ml(mode) || f->dim == 1 || split == kSplitBF16;
     const int var = fixed ? (image_bytes_per_snr(f, split) <= 128 * 1024 ? 4 : 6) : pick_variant(f, total);
-    return shape_cfg(f, n, n_snr, split, var);
+    LaunchCfg c = shape_cfg(f, n, n_snr, split, var);
+    const bool forced = g_variant_override >= 0 && g_variant_override < kNumVariants;
+    c.split_points = split == kSplitF16 && !forced && split_points(f, mode, n, n_snr);
+    return c;
 }
 
 int64_t mfma_blocks_bound(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split) {
@@ -144,15 +155,14 @@ template <int S>
 hipError_t image_and_run(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
                          int mode, float* llr, double* part, uint4* img, int ntiles, LaunchCfg cfg, hipStream_t st) {
     const bool tuned_shape = S == kSplitF16 && !(mode == kModeHd || mode_is_ml(mode) || f->dim == 1);
-    const bool forced = g_variant_override >= 0 && g_variant_override < kNumVariants;
-    MfmaShape shape{MfmaShape::kFixed, 0, image_bytes_per_snr(f, S) <= 128 * 1024, forced};
+    MfmaShape shape{MfmaShape::kFixed, 0, image_bytes_per_snr(f, S) <= 128 * 1024};
     if (S == kSplitBF16 && bf16_wide(f, S)) {
-        shape = {MfmaShape::kWide, 0, false, forced};
+        shape = {MfmaShape::kWide, 0, false};
     } else if (tuned_shape) {
         // the shape mfma_cfg chose for this launch (its block count matches)
         const int var = cfg.variant;
         if (var < 0 || var >= kNumVariants) return hipErrorInvalidValue;
-        shape = {MfmaShape::kVariant, var, kVariants[var].lds && image_bytes_per_snr(f) <= 128 * 1024, forced};
+        shape = {MfmaShape::kVariant, var, kVariants[var].lds && image_bytes_per_snr(f) <= 128 * 1024};
     }
     switch (f->dim) {
         case 1:

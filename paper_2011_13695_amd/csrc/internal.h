@@ -92,6 +92,7 @@ struct LaunchCfg {
     int blocks_per_snr;
     int threads;
     int variant = -1;          // MFMA paths: the launch shape chosen by mfma_cfg
+    bool split_points = false;  // 32 x 32 tiles: a column tile's points over the waves of a block
 };
 
 // ---- launchers (each in the .hip file holding the kernel) ----
@@ -182,7 +183,7 @@ void learned_free(mdgmi_format* fmt);
 // static scratch array here)
 int gmi_with_workspace(const mdgmi_format* fmt, const void* y, const uint32_t* tx_idx, int64_t n,
                        const double* sigma2_host, int32_t n_snr, int32_t path, double* out, void* ws, size_t ws_bytes,
-                       void* stream);
+                       void* stream, int32_t n_plan = 0);
 
 // autotuner table (autotune.hip), per (dim, M) and sample-count regime of
 // the launch (total samples over its SNR points below kTuneShortSamples:

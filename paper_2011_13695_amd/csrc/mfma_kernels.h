@@ -15,7 +15,6 @@ struct MfmaShape {
     enum Kind { kVariant = 0, kFixed = 1, kWide = 2 } kind;
     int var;
     bool lds;
-    bool forced;   // var was asked for by mdgmi_set_tuning: no other shape in its place
 };
 
 // Builds the per-SNR operand images, then runs the demapper kernel.
@@ -109,13 +108,6 @@ __global__ __launch_bounds__(1024) void k_mfma_split(
     double* dst = part + ((int64_t)q_snr * gridDim.x + blockIdx.x) * (MODE == kModeHd ? kNPartHd : kNPart);
     if (MODE == kModeGmi) block_reduce_store(acc, dst);
     if (MODE == kModeHd) block_reduce_store_hd(acc, hd, dst);
-}
-
-// Column tiles of a launch (over its SNR points) up to which the points are
-// split: two per CU. 8-D M = 2048, two points of 1500 samples (94 column tiles): the
-// call 24 us with a wave per tile, 19 us split (48 us with sixteen tiles per block).
-inline bool split_points(int mode, int ntiles, int64_t n, int n_snr) {
-    return !mode_is_ml(mode) && ntiles >= 16 && (n + 31) / 32 * n_snr <= (int64_t)device_cu_count() * 2;
 }
 
 template <int DIM>
@@ -281,7 +273,7 @@ hipError_t mfma_run(const mdgmi_format* f, const float* y, const uint32_t* tx, i
     if (e != hipSuccess) return e;
     const int b = cfg.blocks_per_snr;
     if constexpr (S == kSplitF16) {
-        if (!shape.forced && split_points(mode, ntiles, n, sa.n_snr))
+        if (cfg.split_points)
             return launch_split<DIM>(mode, f, y, tx, n, sa, llr, part, img, ntiles, b, st);
     }
     if constexpr (DIM > 1) {

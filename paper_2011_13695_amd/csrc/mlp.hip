@@ -1215,7 +1215,7 @@ int learned_gmi(const mdgmi_format* fmt, const float* y, const uint32_t* tx_idx,
             }
         } else {
             rc = gmi_with_workspace(fmt, y + (size_t)q0 * n * dim, tx_idx + (size_t)q0 * n, n, sigma2_host + q0,
-                                    q1 - q0, b->exact_path, out + (size_t)q0 * MDGMI_NFIELDS, ws, ws_bytes, stream);
+                                    q1 - q0, b->exact_path, out + (size_t)q0 * MDGMI_NFIELDS, ws, ws_bytes, stream, n_snr);
             if (rc != MDGMI_OK) return rc;
         }
         q0 = q1;
