@@ -95,8 +95,6 @@ GmiPlan plan_gmi(const mdgmi_format* f, int64_t n, int n_snr, int path, int mode
         const int split = path == MDGMI_PATH_F32_MFMA_BF16SPLIT ? 1 : 0;
         p.cfg = mfma_cfg(f, n, n_snr, mode, split);
         p.image_bytes = mfma_image_bytes(f, images, split);
-        if (split == 0 && small_shape_fits(f))
-            p.image_bytes = std::max(p.image_bytes, small_image_bytes(f, std::min(n_snr, kMaxSnrSmall)));
         if (p.cfg.variant == kSmallVariant) p.per_launch = snr_per_launch(n_snr, kMaxSnrSmall);
     }
     int64_t blocks = (int64_t)n_snr * p.cfg.blocks_per_snr;

@@ -95,10 +95,8 @@ bool mfma_supported(const mdgmi_format* f, double max_s, int split) {
 }
 
 size_t mfma_image_bytes(const mdgmi_format* f, int n_snr, int split) {
-    const size_t big = (size_t)n_snr * image_bytes_per_snr(f, split);
-    // either shape may run (the choice follows tuning), so size for both
-    if (split == kSplitF16 && small_shape_fits(f)) return std::max(big, small_image_bytes(f, n_snr));
-    return big;
+    // (the 4x4 shape needs none, but the choice follows tuning: either may run)
+    return (size_t)n_snr * image_bytes_per_snr(f, split);
 }
 
 // Column tiles of a launch (over its SNR points) up to which the points are
@@ -185,7 +183,7 @@ hipError_t launch_mfma(const mdgmi_format* f, const float* y, const uint32_t* tx
                        LaunchCfg cfg, hipStream_t st, int split) {
     const int ntiles = (f->M + 31) / 32;
     uint4* img = (uint4*)image;
-    if (cfg.variant == kSmallVariant) return launch_small(f, y, tx, n, sa, mode, llr, part, image, cfg, st);
+    if (cfg.variant == kSmallVariant) return launch_small(f, y, tx, n, sa, mode, llr, part, cfg, st);
     if (split == kSplitBF16)
         return image_and_run<kSplitBF16>(f, y, tx, n, sa, mode, llr, part, img, ntiles, cfg, st);
     return image_and_run<kSplitF16>(f, y, tx, n, sa, mode, llr, part, img, ntiles, cfg, st);

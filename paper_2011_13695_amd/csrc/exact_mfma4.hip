@@ -16,17 +16,20 @@ using namespace small;
 // for 2^22 samples)
 constexpr int kSmallMaxM = 512, kSmallMaxM8 = 256;
 
-template <int DIM>
-__global__ void k_small_image(const double* __restrict__ X64, int M, SnrArgs sa, uint2* __restrict__ img) {
-    const int q = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= M) return;
-    image_slot<DIM>(X64, sa.s64[q], j, img + ((size_t)q * M + j) * Nk4<DIM>::value);
-}
+// Least waves per SIMD to compile for: the formats of 256 register rows stand within
+// ten registers of the 128 that four waves leave (4-D M = 256 hard decisions of
+// 3 x 10^6 samples: 166 us with three, 159 with four).
+constexpr int small_waves(int dim, int ng) { return dim * ng == 256 && dim < 8 ? 4 : 1; }
 
+// Each block makes the format's A operands itself, in LDS (at most 16 KiB): a slot
+// or two a thread, once, as the launch is one resident round of blocks. A kernel
+// of its own for the images cost a launch per call: 16-QAM calls of 1000 samples
+// 17.5 us, LLRs of them 13.6 us (a good part of either on the host); without it
+// 13.7 and 10.1 us.
 template <int DIM, int NG, int MODE>
-__global__ __launch_bounds__(kSmallThreads) void k_small(const float* __restrict__ y, const uint32_t* __restrict__ tx,
-                                                         const uint2* __restrict__ img, const float* __restrict__ X32,
+__global__ __launch_bounds__(kSmallThreads, small_waves(DIM, NG)) void k_small(const float* __restrict__ y,
+                                                         const uint32_t* __restrict__ tx,
+                                                         const double* __restrict__ X64, const float* __restrict__ X32,
                                                          const uint32_t* __restrict__ labels, int64_t n, SnrArgs sa,
                                                          float max_n2, float* __restrict__ llr,
                                                          double* __restrict__ part) {
@@ -37,11 +40,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const float* __restrict
     const int q_snr = blockIdx.y;
     const float s = sa.s32[q_snr];
     const int64_t snr = sa.snr0 + q_snr;
-    const uint2* __restrict__ gimg = img + (size_t)q_snr * M * NK;
+    __shared__ uint2 img[M * NK];
+    for (int j = threadIdx.x; j < M; j += kSmallThreads) image_slot<DIM>(X64, sa.s64[q_snr], j, img + j * NK);
+    __syncthreads();
     const float* ys = y + snr * n * DIM;
     const uint32_t* txs = mode_is_llr(MODE) ? nullptr : tx + snr * n;
     half4 a[Sets<NG>::value][NK];
-    load_image<DIM, NG>(gimg, M, a);
+    load_image<DIM, NG>(img, M, a);
     CostAcc acc;
     HdAcc hd;
     const float guard = mode_is_llr(MODE) ? llr_guard(s, max_n2) : 0.0f;
@@ -53,7 +58,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const float* __restrict
     SampleIn<DIM> in = load_sample<DIM, MODE>(ys, txs, b * 64 + lane, n);
     for (; b < nbat; b += step) {
         const SampleIn<DIM> next = load_sample<DIM, MODE>(ys, txs, (b + step) * 64 + lane, n);
-        small_sample<DIM, NG, MODE>(a, gimg, in, b * 64 + lane, n, s, X32, labels, llr, acc, hd, guard);
+        small_sample<DIM, NG, MODE>(a, img, in, b * 64 + lane, n, s, X32, labels, llr, acc, hd, guard);
         in = next;
     }
     double* dst = part + ((int64_t)q_snr * gridDim.x + blockIdx.x) * (MODE == kModeHd ? kNPartHd : kNPart);
@@ -63,10 +68,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const float* __restrict
 
 template <int DIM, int NG>
 hipError_t launch_small_t(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
-                          int mode, float* llr, double* part, const uint2* img, int blocks, hipStream_t st) {
+                          int mode, float* llr, double* part, int blocks, hipStream_t st) {
     const dim3 grid(blocks, sa.n_snr), block(kSmallThreads);
 #define MDGMI_SMALL(MD)                                                                                      \
-    hipLaunchKernelGGL((k_small<DIM, NG, MD>), grid, block, 0, st, y, tx, img, f->d_X32,                    \
+    hipLaunchKernelGGL((k_small<DIM, NG, MD>), grid, block, 0, st, y, tx, f->d_X64, f->d_X32,               \
                        MD == kModeHd ? f->d_labels_hd : f->d_labels, n, sa, (float)f->max_norm2, llr, part); \
     break;
     switch (mode) {
@@ -87,25 +92,25 @@ hipError_t launch_small_t(const mdgmi_format* f, const float* y, const uint32_t*
 
 template <int DIM>
 hipError_t launch_small_d(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
-                          int mode, float* llr, double* part, const uint2* img, int blocks, hipStream_t st) {
+                          int mode, float* llr, double* part, int blocks, hipStream_t st) {
     switch (f->M) {
         case 4:
-            return launch_small_t<DIM, 1>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 1>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         case 8:
-            return launch_small_t<DIM, 2>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 2>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         case 16:
-            return launch_small_t<DIM, 4>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 4>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         case 32:
-            return launch_small_t<DIM, 8>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 8>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         case 64:
-            return launch_small_t<DIM, 16>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 16>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         case 128:
-            return launch_small_t<DIM, 32>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 32>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         case 256:
-            return launch_small_t<DIM, 64>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+            return launch_small_t<DIM, 64>(f, y, tx, n, sa, mode, llr, part, blocks, st);
         default:
             if constexpr (DIM < 8) {
-                if (f->M == 512) return launch_small_t<DIM, 128>(f, y, tx, n, sa, mode, llr, part, img, blocks, st);
+                if (f->M == 512) return launch_small_t<DIM, 128>(f, y, tx, n, sa, mode, llr, part, blocks, st);
             }
             return hipErrorInvalidValue;
     }
@@ -144,11 +149,6 @@ bool small_shape_fits(const mdgmi_format* f) {
     const int M = f->M;
     return M >= 4 && (M & (M - 1)) == 0 && (f->dim < 8 ? M <= kSmallMaxM : M <= kSmallMaxM8) &&
            (f->dim == 1 || f->dim == 2 || f->dim == 4 || f->dim == 8);
-}
-
-size_t small_image_bytes(const mdgmi_format* f, int n_snr) {
-    const int nk = (3 * f->dim + 2 + 3) / 4;
-    return (size_t)n_snr * f->M * nk * sizeof(uint2);
 }
 
 // Blocks of (dim, M, mode)'s kernel that a CU holds, from its registers; asked
@@ -195,36 +195,18 @@ LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode) {
 }
 
 hipError_t launch_small(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
-                        int mode, float* llr, double* part, void* image, LaunchCfg cfg, hipStream_t st) {
+                        int mode, float* llr, double* part, LaunchCfg cfg, hipStream_t st) {
     if (!small_shape_fits(f)) return hipErrorInvalidValue;
-    uint2* img = (uint2*)image;
-    const dim3 g((f->M + 63) / 64, sa.n_snr);
-    switch (f->dim) {
-        case 1:
-            hipLaunchKernelGGL(k_small_image<1>, g, dim3(64), 0, st, f->d_X64, f->M, sa, img);
-            break;
-        case 2:
-            hipLaunchKernelGGL(k_small_image<2>, g, dim3(64), 0, st, f->d_X64, f->M, sa, img);
-            break;
-        case 4:
-            hipLaunchKernelGGL(k_small_image<4>, g, dim3(64), 0, st, f->d_X64, f->M, sa, img);
-            break;
-        default:
-            hipLaunchKernelGGL(k_small_image<8>, g, dim3(64), 0, st, f->d_X64, f->M, sa, img);
-            break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int b = cfg.blocks_per_snr;
     switch (f->dim) {
         case 1:
-            return launch_small_d<1>(f, y, tx, n, sa, mode, llr, part, img, b, st);
+            return launch_small_d<1>(f, y, tx, n, sa, mode, llr, part, b, st);
         case 2:
-            return launch_small_d<2>(f, y, tx, n, sa, mode, llr, part, img, b, st);
+            return launch_small_d<2>(f, y, tx, n, sa, mode, llr, part, b, st);
         case 4:
-            return launch_small_d<4>(f, y, tx, n, sa, mode, llr, part, img, b, st);
+            return launch_small_d<4>(f, y, tx, n, sa, mode, llr, part, b, st);
         default:
-            return launch_small_d<8>(f, y, tx, n, sa, mode, llr, part, img, b, st);
+            return launch_small_d<8>(f, y, tx, n, sa, mode, llr, part, b, st);
     }
 }
 

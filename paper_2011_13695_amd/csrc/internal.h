@@ -47,7 +47,7 @@ __host__ __device__ constexpr bool mode_is_ml(int mode) { return mode == kModeMl
 // what the final reduction writes: GMI/MI, + hard decisions, or GMI only
 constexpr int kReduceGmi = 0, kReduceHd = 1, kReduceMl = 2;
 constexpr int kMaxSnrPerLaunch = 32;
-// ... and of the per-sample 4x4 shape: its images are small, and with a quarter of
+// ... and of the per-sample 4x4 shape, which keeps no images: with a quarter of
 // a round of blocks lost at each launch's end, one launch of 41 points of 131071
 // 16-QAM samples took 42.5 us where two of 21 and 20 took 52
 constexpr int kMaxSnrSmall = 64;
@@ -117,10 +117,9 @@ bool small_shape_fits(const mdgmi_format* f);
 // whether the fp16-split path runs f on that shape in launches of many
 // samples (tuning table, override): the ragged batch's choice
 bool prefers_small(const mdgmi_format* f);
-size_t small_image_bytes(const mdgmi_format* f, int n_snr);
 LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode);
 hipError_t launch_small(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
-                        int mode, float* llr, double* part, void* image, LaunchCfg cfg, hipStream_t st);
+                        int mode, float* llr, double* part, LaunchCfg cfg, hipStream_t st);
 
 // split: 0 = fp16 hi + lo operands, 1 = bf16 in three parts (see mfma_core.h)
 bool mfma_supported(const mdgmi_format* f, double max_s, int split = 0);
