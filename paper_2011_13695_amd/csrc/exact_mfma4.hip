@@ -182,11 +182,16 @@ static int small_blocks_per_cu(int dim, int M, int mode) {
 // 2^22 samples 58 us, now 55; 16-QAM hard decisions, 41 points of 131071
 // samples, 60 us (as 32 + 9 points), now 42.5 (in one launch). Calls of very many
 // points keep four, and with it the partial sums they had room for.
+int64_t small_blocks(const mdgmi_format* f, int n_snr, int mode) {
+    const int per_cu = small_blocks_per_cu(f->dim, f->M, mode);
+    return (int64_t)device_cu_count() * (n_snr <= 8 * kMaxSnrPerLaunch ? per_cu : std::min(per_cu, 4));
+}
+
+int64_t small_want(int64_t n) { return (n + kSmallThreads - 1) / kSmallThreads; }
+
 LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode) {
-    const int64_t batches = (n + 63) / 64;
-    const int64_t want = (batches + kSmallThreads / 64 - 1) / (kSmallThreads / 64);
-    const int per_cu = n_snr <= 8 * kMaxSnrPerLaunch ? small_blocks_per_cu(f->dim, f->M, mode) : 4;
-    int64_t per = std::max<int64_t>(1, (int64_t)device_cu_count() * per_cu / snr_per_launch(n_snr, kMaxSnrSmall));
+    const int64_t want = small_want(n);
+    int64_t per = std::max<int64_t>(1, small_blocks(f, n_snr, mode) / snr_per_launch(n_snr, kMaxSnrSmall));
     per = std::min<int64_t>(per, std::max<int64_t>(1, want));
     LaunchCfg c;
     c.threads = kSmallThreads;

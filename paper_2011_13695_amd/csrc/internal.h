@@ -118,6 +118,8 @@ bool small_shape_fits(const mdgmi_format* f);
 // samples (tuning table, override): the ragged batch's choice
 bool prefers_small(const mdgmi_format* f);
 LaunchCfg small_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode);
+int64_t small_blocks(const mdgmi_format* f, int n_snr, int mode);  // of a launch, where there is work for them
+int64_t small_want(int64_t n);                                    // blocks that have work at one point
 hipError_t launch_small(const mdgmi_format* f, const float* y, const uint32_t* tx, int64_t n, const SnrArgs& sa,
                         int mode, float* llr, double* part, LaunchCfg cfg, hipStream_t st);
 
