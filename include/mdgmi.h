@@ -331,8 +331,8 @@ int mdgmi_gmi_static(const mdgmi_format* fmt, const void* y, const uint32_t* tx_
 
 /* ---- ragged batches ------------------------------------------------------
  * Many (format, SNR, sample count) instances evaluated by one persistent
- * kernel: the samples of every instance are cut into items of about 2^22
- * sample*points, a persistent grid pulls items from an atomic counter and
+ * kernel: the samples of every instance are cut into items of at most about
+ * 2^22 sample*points, a persistent grid pulls items from an atomic counter and
  * dispatches each to the direct or MFMA code of its (dim, M); per-item FP64
  * partials are reduced per instance in item order (bit-reproducible). */
 typedef struct {
