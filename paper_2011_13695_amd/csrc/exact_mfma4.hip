@@ -179,8 +179,9 @@ static int small_blocks_per_cu(int dim, int M, int mode) {
 // One resident round of blocks over the launch's SNR points, as many per CU as
 // the kernel's registers allow (3 to 8). Four per CU for every format left the
 // light ones waiting on their loads and dependent operations: 64-QAM LLRs of
-// 2^22 samples 58 us, now 55; 16-QAM hard decisions, 41 points of 131071
-// samples, 60 us (as 32 + 9 points), now 42.5 (in one launch). Calls of very many
+// 2^22 samples 58 us with four, 55 so (52.9 since the images are made here); 16-QAM
+// hard decisions, 41 points of 131071 samples, 60 us with four in launches of 32
+// and 9 points, 42.5 so in one launch (39.2 since, with max_u). Calls of very many
 // points keep four, and with it the partial sums they had room for.
 int64_t small_blocks(const mdgmi_format* f, int n_snr, int mode) {
     const int per_cu = small_blocks_per_cu(f->dim, f->M, mode);
