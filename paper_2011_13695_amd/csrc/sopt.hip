@@ -289,7 +289,13 @@ __global__ __launch_bounds__(kSearchThreads) void k_sopt_rest(const T* __restric
     __shared__ uint32_t s_ticket, s_last;
     uint32_t* sync = (uint32_t*)(state + kStSync);
     state += (kSoptAhead & 1) * kStLen;
-    if (get(state + kStOver) != 0.0) return;
+    // one thread looks for the block: where the block starts late, the last pass
+    // may be publishing its state at this moment, and of waves that go by their own
+    // reads some could leave and the rest wait for a ticket nobody draws (once the
+    // word is set, every share of every pass has been drawn and summed)
+    if (threadIdx.x == 0) s_last = get(state + kStOver) != 0.0 ? 1u : 0u;
+    __syncthreads();
+    if (s_last != 0u) return;
     for (;;) {
         if (threadIdx.x == 0) {
             const uint32_t t = __hip_atomic_fetch_add(sync + kSyncTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
