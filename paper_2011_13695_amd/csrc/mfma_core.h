@@ -517,13 +517,14 @@ __device__ __forceinline__ void full_sums(const float* p0, const float* p1, int 
 // common offset (its sum below 2^kFarLog2): classes that were in range keep
 // their first-pass sums; the far ones are summed again with the offset
 // raised by 100 (the same fold, the exponents of the near points capped);
-// classes still out of range, or non-finite inputs, take the exact
-// per-class path. p0/p1 are the first pass's partials of this lane.
+// classes still out of range, samples beyond the split's range (in_range false)
+// and non-finite inputs take the exact per-class path. p0/p1 are the first pass's
+// partials of this lane.
 template <int DIM, int G, int MAXHI, int S = kSplitF16>
 __device__ __forceinline__ void llr_far_pass(const uint4* __restrict__ A, const float* __restrict__ ys, int64_t n,
                                           int64_t i, int M, int m, int ntiles, float s,
                                           const float* __restrict__ X32, float* __restrict__ llr, const float* p0,
-                                          const float* p1) {
+                                          const float* p1, bool in_range) {
     constexpr int NB = Blk<DIM, S>::value;
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5, col = lane & 31;
@@ -561,7 +562,7 @@ __device__ __forceinline__ void llr_far_pass(const uint4* __restrict__ A, const 
     float q0[MDGMI_MAX_BITS], q1[MDGMI_MAX_BITS];
     half_partials<MAXHI, G>(bank[0], hi[0], m, q0, q1);
     float out[NJ];
-    bool bad = false;
+    bool bad = !in_range;  // the second pass clamps its NaN u to finite sums
 #pragma unroll
     for (int j = 0; j < NJ; j++) {
         out[j] = 0.0f;
@@ -642,10 +643,12 @@ __device__ __forceinline__ void mfma_finish(const uint4* __restrict__ A, const f
             }
         }
         // a class of some sample of this column lies too far for the
-        // common offset (or y is not finite): second pass for the column
-        // (columns past n, at y = 0, do not count)
-        if (__ballot(i < n && !(smin >= ex2(kFarLog2))) != 0ull) {
-            llr_far_pass<DIM, G, MAXHI, S>(A, ys, n, i, M, m, ntiles, s, X32, llr, p0, p1);
+        // common offset, or y is beyond the range of its split or not finite
+        // (all its u are NaN then, which fminf drops: the total tells):
+        // second pass for the column (columns past n, at y = 0, do not count)
+        const bool in_range = tot == tot;
+        if (__ballot(i < n && !(smin >= ex2(kFarLog2) && in_range)) != 0ull) {
+            llr_far_pass<DIM, G, MAXHI, S>(A, ys, n, i, M, m, ntiles, s, X32, llr, p0, p1, in_range);
             return;
         }
         constexpr int NJ = (MDGMI_MAX_BITS + 1) / 2;
