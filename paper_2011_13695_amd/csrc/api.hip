@@ -326,7 +326,10 @@ int mdgmi_llr_workspace_size(const mdgmi_format* fmt, int64_t n, int32_t path, s
     if (!fmt || !bytes) return MDGMI_E_NULL;
     if (n < 1) return MDGMI_E_SHAPE;
     if (path == MDGMI_PATH_LEARNED_BF16) return learned_llr_workspace_size(fmt, n, bytes);
-    int p = path == MDGMI_PATH_AUTO ? (fmt->M >= 32 ? MDGMI_PATH_F32_MFMA_F16SPLIT : MDGMI_PATH_F32_DIRECT) : path;
+    // AUTO: sized for every path that resolve_path may choose for the format
+    int p = path;
+    if (path == MDGMI_PATH_AUTO)
+        p = fmt->M >= 32 || small_shape_fits(fmt) ? MDGMI_PATH_F32_MFMA_F16SPLIT : MDGMI_PATH_F32_DIRECT;
     if (p == MDGMI_PATH_F64)
         *bytes = 0;
     else if (p == MDGMI_PATH_F32_DIRECT)
