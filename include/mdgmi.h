@@ -227,7 +227,12 @@ int mdgmi_gmi_maxlog(const mdgmi_format* fmt, const void* y, const uint32_t* tx_
  *   ws       device workspace of mdgmi_gmi_sopt_workspace_size bytes
  * A non-finite LLR or a sent row outside [0, M) makes every estimate NaN
  * (counted in MDGMI_S_NONFINITE). LLRs that favour the wrong bit on average
- * give s* = 0 and GMI = 0. */
+ * give s* = 0 and GMI = 0. MDGMI_S_GMI is the largest GMI(s) among the points
+ * evaluated, s = 1 among them, so never below MDGMI_S_GMI1; s* is that point,
+ * or its neighbour (within 6e-3 s* for FP32 LLRs, 3e-7 s* for FP64) that the
+ * derivative led to later, where the costs' rounding does not tell the two
+ * apart. LLRs without an error have no finite optimum: s* is then the first
+ * point at which the GMI is the largest. */
 enum {
     MDGMI_S_GMI1 = 0,      /* GMI at s = 1 (the LLRs as given)            */
     MDGMI_S_SE1 = 1,       /* its standard error                          */

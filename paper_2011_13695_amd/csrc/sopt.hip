@@ -36,12 +36,13 @@ constexpr int kSoptPart = 6;      // sum C, sum C^2, sum C', sum C'', sum v, non
 constexpr int kSoptPasses = 64;
 constexpr int kSoptAhead = 6;    // matched and scaled Gaussian LLRs converge in 3-5
 constexpr int kSearchThreads = 512;
-// state of the search: s, lo, hi, passes done, best GMI so far, ended. Two
-// slots, written in turn; then the words that order the passes of k_sopt_rest:
-// the next ticket, the shares done, the passes published.
-constexpr int kStS = 0, kStLo = 1, kStHi = 2, kStIter = 3, kStBest = 4, kStOver = 5, kStLen = 6;
+// state of the search: s, lo, hi, passes done, best GMI so far, ended, the s
+// reported so far. Two slots, written in turn; then the words that order the
+// passes of k_sopt_rest: the next ticket, the shares done, the passes published.
+constexpr int kStS = 0, kStLo = 1, kStHi = 2, kStIter = 3, kStBest = 4, kStOver = 5, kStRowS = 6, kStLen = 7;
 constexpr int kStSync = 2 * kStLen, kStateLen = 16;
-constexpr int kSyncTicket = 0, kSyncDone = 1, kSyncPass = 2;
+constexpr int kSyncTicket = 0, kSyncDone = 1, kSyncPass = 2, kSyncLen = 3;
+static_assert(kStSync * sizeof(double) + kSyncLen * sizeof(uint32_t) <= kStateLen * sizeof(double), "state layout");
 constexpr uint32_t kSoptOver = 0xffffffffu;  // passes published, once the search has ended
 
 // Values that blocks of k_sopt_rest hand to each other (partial sums, state, the
@@ -132,14 +133,20 @@ __device__ void sopt_update(const double* tot, const double* now, int64_t n, int
             return;
         }
     }
-    // keep the best point evaluated; among points that the precision of the
-    // costs does not tell apart the later one, which the derivative led to
-    if (gmi > now[kStBest] - flat * m) {
-        next[kStBest] = fmax(gmi, now[kStBest]);
-        put_row(MDGMI_S_S, s);
+    // keep the best point evaluated. Around the optimum the costs' rounding
+    // decides which of two neighbouring points looks better (a step of relative
+    // size d changes the GMI by at most d^2 / 3 a bit), while the derivative still
+    // tells them apart: s follows it there, the GMI reported stays the largest.
+    const bool better = gmi > now[kStBest];
+    if (better) {
+        next[kStBest] = gmi;
         put_row(MDGMI_S_GMI, gmi);
         put_row(MDGMI_S_SE, se);
         put_row(MDGMI_S_NGMI, gmi / m);
+    }
+    if (better || (gmi > now[kStBest] - flat * m && fabs(s - now[kStRowS]) <= 16.0 * sqrt(flat) * s)) {
+        next[kStRowS] = s;
+        put_row(MDGMI_S_S, s);
     }
     put_row(MDGMI_S_ITERS, it + 1);
     next[kStIter] = it + 1;
@@ -228,6 +235,7 @@ __device__ __forceinline__ void sopt_step(int p, int shares, int64_t n, int m, d
             now[kStIter] = 0.0;
             now[kStBest] = -INFINITY;
             now[kStOver] = 0.0;
+            now[kStRowS] = 0.0;
         }
         if (keep && threadIdx.x < MDGMI_NFIELDS_S) out[threadIdx.x] = NAN;
     } else if (before[kStOver] != 0.0) {
