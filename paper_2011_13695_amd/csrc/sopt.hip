@@ -83,8 +83,10 @@ __device__ __forceinline__ void term(float v, float s, float& mx, float& P, floa
 }
 
 __device__ __forceinline__ void term(double v, double s, double& mx, double& P, double& d1, double& d2) {
-    const double z = s * v;
-    const double e = f64::exp_neg(fabs(z), f64::exp_scale_unit());
+    const double z = s * v, az = fabs(z);
+    // exp_neg stays at 2^-1000 from |z| = 693 on; the derivatives have to reach 0, or
+    // a search among LLRs without an error would go on for all its passes
+    const double e0 = f64::exp_neg(az, f64::exp_scale_unit()), e = az > 693.0 ? 0.0 : e0;
     const double p = f64::fast_div(1.0, 1.0 + e);
     mx += z > 0.0 ? 0.0 : -z;
     P += fma(e, P, e);

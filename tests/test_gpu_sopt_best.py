@@ -1,6 +1,6 @@
 """What an s search reports: never less than the GMI at s = 1 that it has
 evaluated, and for LLRs without an error, whose cost falls for ever, the first
-scale at which the GMI is m."""
+scale at which the GMI is m, in one pass where nothing is left to gain."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ if not torch.cuda.is_available():
 
 from paper_2011_13695_amd import mdgmi  # noqa: E402
 
-GMI1, S, GMI, NGMI = 0, 2, 3, 5
+GMI1, S, GMI, NGMI, ITERS = 0, 2, 3, 5, 8
 
 
 def case(m, n, seed):
@@ -41,7 +41,7 @@ def test_not_below_a_point_evaluated(m, n):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
-@pytest.mark.parametrize("lo,hi", [(50.0, 50.0), (50.0, 90.0), (60.0, 600.0)])
+@pytest.mark.parametrize("lo,hi", [(50.0, 50.0), (50.0, 90.0), (60.0, 600.0), (800.0, 1e4), (1e5, 1e9)])
 def test_without_errors(dtype, lo, hi):
     m, n = 4, 2001
     rng, gf, tx, sign = case(m, n, 3)
@@ -49,3 +49,5 @@ def test_without_errors(dtype, lo, hi):
     print(f"[sopt best] no errors {dtype} {lo} {hi}", flush=True)
     a = mdgmi.mdgmi_gmi_sopt(gf, lam, tx).cpu().numpy()
     assert a[GMI1] == m and a[GMI] == m and a[S] == 1.0
+    if lo >= 800.0:  # every exponential is 0: so is the slope
+        assert a[ITERS] == 1
