@@ -79,14 +79,15 @@ LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int split, int 
     const MfmaVariant& v = shape_of(var);
     const int64_t cols = 32 * v.ncol;
     const int64_t tiles = (n + cols - 1) / cols;
-    const int64_t want = n_snr <= kMaxSnrPerLaunch ? tiles : (tiles + v.waves - 1) / v.waves;
     const int64_t total = shape_blocks(f, split, var);
     const int snr_in_launch = snr_per_launch(n_snr);
     int64_t per = std::max<int64_t>(1, total / snr_in_launch);
-    // a short call takes a block per column tile as far as there are CUs: the
-    // tiles go to the blocks in turn, a wave or two of each has work, and a SIMD
-    // with one busy wave is through its tile in a third of the time
-    per = std::min<int64_t>(per, std::max<int64_t>(1, want));
+    // a launch of few samples takes a block per column tile as far as there are
+    // CUs: the tiles go to the blocks in turn, a wave or two of each has work, and
+    // a SIMD with one busy wave is through its tile in a third of the time. By the
+    // launch's points, not the call's: 8-D M = 2048, 40 points of 700 samples (two
+    // launches of 440 tiles) 98 us with sixteen tiles per block, 56 us so
+    per = std::min(per, tiles);
     LaunchCfg c;
     c.threads = v.waves * 64;
     c.blocks_per_snr = (int)per;

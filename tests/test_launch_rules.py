@@ -1,0 +1,62 @@
+"""Launch rules of the matrix-core kernels, on the CPU, over formats, modes, numbers
+of points and samples: where a tile's points are split over a block's waves, the
+block has few tiles to take one after another, also in calls of more points than
+a launch takes."""
+import shutil
+import subprocess
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parent.parent
+LIB = ROOT / "paper_2011_13695_amd" / "libmdgmi.so"
+CUS = 256                       # of the device, or where there is none
+ML = (3, 4)
+WIDE = {-1: 2, 1: 2, 3: 2}      # sample columns per wave of a shape, 1 in the others
+SMALL = 8                       # the 4x4 shape
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if not shutil.which("hipcc") or not LIB.exists():
+        pytest.skip("hipcc or the built library not available")
+    exe = tmp_path_factory.mktemp("launch") / "driver"
+    subprocess.run(["hipcc", "-std=c++17", "-O1", "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    str(ROOT / "tests" / "sanitize" / "launch_driver.cpp"), "-x", "none", str(LIB),
+                    f"-Wl,-rpath,{LIB.parent}", "-o", str(exe)], check=True)
+
+    def ask(forms):
+        r = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, f)) for f in forms), capture_output=True,
+                           text=True, check=True, timeout=300)
+        return [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
+    return ask
+
+
+def forms():
+    points = [1, 2, 3, 7, 16, 20, 30, 31, 32, 33, 40, 41, 64, 65, 100, 129, 256, 300]
+    samples = [1, 31, 32, 33, 100, 300, 700, 1500, 2049, 5000, 8192, 8193, 12000, 16384, 20000, 100000, 1000003]
+    for dim, M in [(1, 1024), (2, 32), (2, 1024), (4, 512), (4, 4096), (8, 32), (8, 512), (8, 2048), (8, 4096)]:
+        for split in (0, 1):
+            for mode in range(5):
+                for n_snr in ([1] if mode in (1, 3) else points):
+                    for n in samples:
+                        yield dim, M, split, mode, n_snr, n
+
+
+def per_launch(n_snr):
+    launches = -(-n_snr // 32)
+    return -(-n_snr // launches)
+
+
+def test_split_points(rules):
+    fs = list(forms())
+    split = 0
+    for f, (blocks, threads, variant, sp) in zip(fs, rules(fs)):
+        if not sp:
+            continue
+        split += 1
+        dim, M, s, mode, n_snr, n = f
+        tiles = -(-n // 32)
+        assert s == 0 and mode not in ML and M >= 512, f
+        assert tiles * per_launch(n_snr) <= 2 * CUS and -(-tiles // blocks) <= 3, (f, blocks)
+    assert split > 1000
