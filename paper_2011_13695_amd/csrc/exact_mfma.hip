@@ -110,12 +110,22 @@ size_t mfma_image_bytes(const mdgmi_format* f, int n_snr, int split) {
     return (size_t)n_snr * image_bytes_per_snr(f, split);
 }
 
+// Blocks of a launch of the kernel that splits a tile's points: two per CU, one
+// where a block is sixteen waves (M = 4096: all a CU holds at 128 registers).
+static int64_t split_blocks(const mdgmi_format* f) {
+    return (int64_t)device_cu_count() * (f->M > 2048 ? 1 : 2);
+}
+
 // Column tiles of a launch (over its SNR points) up to which the points are
 // split: two per CU. 8-D M = 2048, two points of 1500 samples (94 column tiles): the
 // call 24 us with a wave per tile, 19 us split (48 us with sixteen tiles per block).
+// LLRs only with a block for each tile: one wave of a block ends its tile, and
+// samples that take the per-class path there (2.5 ms at M = 2048) wait for each
+// other: M = 2048, 28 dB, 257 to 512 tiles, two per block 5.0 ms, with a wave per
+// tile or two blocks per CU 2.5 ms.
 static bool split_points(const mdgmi_format* f, int mode, int64_t n, int n_snr) {
-    return !mode_is_ml(mode) && (f->M + 31) / 32 >= 16 &&
-           (n + 31) / 32 * snr_per_launch(n_snr) <= (int64_t)device_cu_count() * 2;
+    const int64_t most = mode_is_llr(mode) ? split_blocks(f) : (int64_t)device_cu_count() * 2;
+    return !mode_is_ml(mode) && (f->M + 31) / 32 >= 16 && (n + 31) / 32 * snr_per_launch(n_snr) <= most;
 }
 
 LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split) {
@@ -133,6 +143,8 @@ LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int sp
     LaunchCfg c = shape_cfg(f, n, n_snr, split, var);
     const bool forced = g_variant_override >= 0 && g_variant_override < kNumVariants;
     c.split_points = split == kSplitF16 && !forced && split_points(f, mode, n, n_snr);
+    if (c.split_points)
+        c.blocks_per_snr = (int)std::max<int64_t>(1, std::min((n + 31) / 32, split_blocks(f) / snr_per_launch(n_snr)));
     return c;
 }
 
@@ -149,6 +161,7 @@ int64_t mfma_blocks_bound(const mdgmi_format* f, int64_t n, int n_snr, int mode,
     int64_t b = 0;
     for (int v = -1; v < kNumVariants; v++)
         b = std::max(b, bound(kMaxSnrPerLaunch, shape_blocks(f, split, v), (n + 31) / 32));
+    if (split == kSplitF16) b = std::max(b, bound(kMaxSnrPerLaunch, split_blocks(f), (n + 31) / 32));
     if (split == kSplitF16 && small_shape_fits(f))
         b = std::max(b, bound(kMaxSnrSmall, small_blocks(f, 1, mode), small_want(n)));
     return b;

@@ -1,7 +1,7 @@
 """Launch rules of the matrix-core kernels, on the CPU, over formats, modes, numbers
 of points and samples: where a tile's points are split over a block's waves, the
 block has few tiles to take one after another, also in calls of more points than
-a launch takes."""
+a launch takes; a block of LLRs, whose slow samples one wave ends, has one."""
 import shutil
 import subprocess
 from pathlib import Path
@@ -58,5 +58,7 @@ def test_split_points(rules):
         dim, M, s, mode, n_snr, n = f
         tiles = -(-n // 32)
         assert s == 0 and mode not in ML and M >= 512, f
-        assert tiles * per_launch(n_snr) <= 2 * CUS and -(-tiles // blocks) <= 3, (f, blocks)
+        assert tiles * per_launch(n_snr) <= 2 * CUS and -(-tiles // blocks) <= (1 if mode == 1 else 3), (f, blocks)
+        # both of a CU's blocks fit beside each other: sixteen waves of 128 registers
+        assert blocks * per_launch(n_snr) <= CUS * max(16 // (M // 256), 1) or blocks == 1, (f, blocks)
     assert split > 1000
