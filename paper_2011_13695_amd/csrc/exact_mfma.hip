@@ -61,33 +61,52 @@ const MfmaVariant& shape_of(int var) {
     return var < 0 ? wide : kVariants[var];
 }
 
+// Waves of 32 x 32 shape v that a CU holds, by the registers of its kernels (as
+// the compiler reports them): two-column shapes 153 to 256, those of sixteen
+// waves are held to 128, the others up to 122 for GMI of 1 to 4 dimensions and up
+// to 170 otherwise.
+int shape_waves(const mdgmi_format* f, const MfmaVariant& v, int mode) {
+    if (v.ncol == 2) return 8;
+    if (v.waves == 16 || (mode == kModeGmi && f->dim <= 4 && v.lds)) return 16;
+    return 12;
+}
+
 // Blocks of a launch of 32 x 32 shape var: one resident round over all CUs, the
-// blocks per CU limited by the LDS image (160 KiB per CU) and by a target of 16
-// waves per CU.
-int64_t shape_blocks(const mdgmi_format* f, int split, int var) {
+// blocks per CU limited by the LDS image (160 KiB per CU) and by the waves (cu_waves)
+// that fit. Counted at sixteen waves for every shape, a launch of a block per tile ran
+// in two rounds of part blocks where they do not fit: 8-D M = 2048 in the bf16 split
+// (two columns, 256 registers), 313 column tiles, LLRs 57 us, and 10 ms with
+// samples on the per-class path; now 34 us and 5.1 ms (eight tiles per block: 49 us
+// and 5.3 ms).
+int64_t shape_blocks(const mdgmi_format* f, int split, int var, int cu_waves) {
     const MfmaVariant& v = shape_of(var);
     const size_t img = image_bytes_per_snr(f, split);
     const bool lds = v.lds && img <= 128 * 1024;
     const int by_lds = lds ? std::max(1, (int)((160 * 1024) / (img + 2048))) : 8;
-    const int by_waves = std::max(1, 16 / v.waves);
+    const int by_waves = std::max(1, cu_waves / v.waves);
     return (int64_t)device_cu_count() * std::min(by_lds, by_waves);
 }
 
 // Launch configuration of 32 x 32 shape var (-1: the bf16 split's
 // two-column L2 shape).
-LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int split, int var) {
+LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int split, int var) {
     const MfmaVariant& v = shape_of(var);
     const int64_t cols = 32 * v.ncol;
     const int64_t tiles = (n + cols - 1) / cols;
-    const int64_t total = shape_blocks(f, split, var);
+    const int64_t round = shape_blocks(f, split, var, shape_waves(f, v, mode));
     const int snr_in_launch = snr_per_launch(n_snr);
-    int64_t per = std::max<int64_t>(1, total / snr_in_launch);
-    // a launch of few samples takes a block per column tile as far as there are
-    // CUs: the tiles go to the blocks in turn, a wave or two of each has work, and
-    // a SIMD with one busy wave is through its tile in a third of the time. By the
-    // launch's points, not the call's: 8-D M = 2048, 40 points of 700 samples (two
-    // launches of 440 tiles) 98 us with sixteen tiles per block, 56 us so
-    per = std::min(per, tiles);
+    // a launch of few samples takes a block per column tile as far as they fit
+    // beside each other: the tiles go to the blocks in turn, a wave or two of each
+    // has work, and a SIMD with one busy wave is through its tile in a third of the
+    // time. By the launch's points, not the call's: 8-D M = 2048, 40 points of 700
+    // samples (two launches of 440 tiles) 98 us with sixteen tiles per block, 56 us so
+    int64_t per = std::min(round / snr_in_launch, tiles);
+    // LLR blocks do not end together in a reduction: up to sixteen waves per CU
+    // with a tile each, also where they run behind each other (2-D M = 1024, 2.5e6
+    // samples: 360 us, 378 in one round of eight waves per CU)
+    if (mode_is_llr(mode))
+        per = std::max(per, std::min((tiles + v.waves - 1) / v.waves, shape_blocks(f, split, var, 16) / snr_in_launch));
+    per = std::max<int64_t>(1, per);
     LaunchCfg c;
     c.threads = v.waves * 64;
     c.blocks_per_snr = (int)per;
@@ -135,12 +154,12 @@ LaunchCfg mfma_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int sp
         c.variant = kSmallVariant;
         return c;
     }
-    if (bf16_wide(f, split)) return shape_cfg(f, n, n_snr, split, -1);
+    if (bf16_wide(f, split)) return shape_cfg(f, n, n_snr, mode, split, -1);
     // hard decisions, max-log metrics, 1-D formats and the bf16 split run the
     // 1-column, 16-wave shape only (LDS image if it fits)
     const bool fixed = mode == kModeHd || mode_is_ml(mode) || f->dim == 1 || split == kSplitBF16;
     const int var = fixed ? (image_bytes_per_snr(f, split) <= 128 * 1024 ? 4 : 6) : pick_variant(f, total);
-    LaunchCfg c = shape_cfg(f, n, n_snr, split, var);
+    LaunchCfg c = shape_cfg(f, n, n_snr, mode, split, var);
     const bool forced = g_variant_override >= 0 && g_variant_override < kNumVariants;
     c.split_points = split == kSplitF16 && !forced && split_points(f, mode, n, n_snr);
     if (c.split_points)
@@ -160,7 +179,7 @@ int64_t mfma_blocks_bound(const mdgmi_format* f, int64_t n, int n_snr, int mode,
     };
     int64_t b = 0;
     for (int v = -1; v < kNumVariants; v++)
-        b = std::max(b, bound(kMaxSnrPerLaunch, shape_blocks(f, split, v), (n + 31) / 32));
+        b = std::max(b, bound(kMaxSnrPerLaunch, shape_blocks(f, split, v, shape_waves(f, shape_of(v), mode)), (n + 31) / 32));
     if (split == kSplitF16) b = std::max(b, bound(kMaxSnrPerLaunch, split_blocks(f), (n + 31) / 32));
     if (split == kSplitF16 && small_shape_fits(f))
         b = std::max(b, bound(kMaxSnrSmall, small_blocks(f, 1, mode), small_want(n)));

@@ -12,7 +12,7 @@ ROOT = Path(__file__).resolve().parent.parent
 LIB = ROOT / "paper_2011_13695_amd" / "libmdgmi.so"
 CUS = 256                       # of the device, or where there is none
 ML = (3, 4)
-WIDE = {-1: 2, 1: 2, 3: 2}      # sample columns per wave of a shape, 1 in the others
+WIDE = (-1, 1, 3)               # shapes of two sample columns per wave
 SMALL = 8                       # the 4x4 shape
 
 
@@ -62,3 +62,23 @@ def test_split_points(rules):
         # both of a CU's blocks fit beside each other: sixteen waves of 128 registers
         assert blocks * per_launch(n_snr) <= CUS * max(16 // (M // 256), 1) or blocks == 1, (f, blocks)
     assert split > 1000
+
+
+def test_one_resident_round(rules):
+    """Blocks of a launch fit beside each other: of the bf16 split's two-column
+    shape (256 registers) one of eight waves per CU, of the one-column shapes of
+    eight waves two for GMI of up to four dimensions (122), else one. Launches of LLRs
+may have more, of which every wave has work."""
+    fs = list(forms())
+    seen = 0
+    for f, (blocks, threads, variant, sp) in zip(fs, rules(fs)):
+        if variant == SMALL or sp:
+            continue
+        dim, M, s, mode, n_snr, n = f
+        waves = threads // 64
+        fit = 8 if variant in WIDE else 16 if waves == 16 or (mode == 0 and dim <= 4) else 12
+        full = -(-n // (32 * (2 if variant in WIDE else 1) * waves))  # blocks whose waves all have a tile
+        beside = CUS * max(1, fit // waves) // per_launch(n_snr)
+        assert blocks <= max(1, beside, full if mode in (1, 3) else 0), (f, blocks, threads)
+        seen += 1
+    assert seen > 1000
