@@ -200,25 +200,103 @@ int batch_kind_for(const mdgmi_format* f, double s, int path) {
 // two, from their instruction counts).
 static int64_t sample_cost(int kind, int M) { return M + (kind == kKindMfma ? 200 : 40); }
 
-// Item sizes per kind, in sample_cost units. A kind's blocks (one per CU for
-// 32 x 32 tiles, about two otherwise) each get at least eight items where the
-// batch is large enough, so that they end together; an item is at most
-// max_pairs, and at least several times its overheads (the pull, the operand
-// image, the FP64 reduction: 2-4 us) at the kind's rate per block (3e10 and
-// 9e9 points/s): a set of 748 items of 4x4-shape instances took 69, 49 and 47 us
-// with 30000, 100000 and 200000; one 8-D M = 512 instance 36, 45 and 70 us with
-// 400000, 800000 and 1600000. With max_pairs alone (2^22) an instance of 2e5
-// samples and M = 4 was one block's work. 48 instances of 1e3..2e5 samples,
-// M = 8..4096: 803 us then, 240 us now (the tail lanes' share of that: see
-// small_core.h).
-static void item_costs(const mdgmi_instance* inst, const std::vector<int>& kind, int64_t max_pairs,
-                       int64_t (&cost)[3]) {
+// Samples of a kind's items: size / (M + extra), in whole multiples of align.
+struct ItemSize {
+    int64_t size;
+    int extra, align;
+    int64_t samples(int M) const { return std::max<int64_t>(align, size / (M + extra) / align * align); }
+};
+
+// Time, in points, after which the last block of the 32 x 32 kind is through its
+// items: each goes, in launch order, to the block that is free first.
+// insts: (samples, M). Gives up (INT64_MAX) where it cannot be below `best`.
+static int64_t batch_span(const std::vector<std::pair<int64_t, int>>& insts, const ItemSize& z, int blocks,
+                          int64_t best) {
+    // 512 samples of an item take M + 300 points' time each at 3.2e10 points/s (from
+    // 13 us at 8-D M = 512 to 70 at 4-D M = 4096), an item 8 us more: the pull, the
+    // FP64 reduction, and the set-up and end that no other tile hides
+    constexpr int64_t kItemOverhead = 256000;
+    auto cost = [&](int64_t s, int M) { return (s + z.align - 1) / z.align * z.align * (M + 300) + kItemOverhead; };
+    int64_t all = 0;
+    for (const auto& q : insts) {
+        const int64_t per = z.samples(q.second);
+        all += q.first / per * cost(per, q.second) + (q.first % per ? cost(q.first % per, q.second) : 0);
+    }
+    if (all / blocks >= best) return INT64_MAX;
+    std::vector<int64_t> free_at(blocks, 0);  // a heap, the earliest first
+    int64_t base = 0, end = 0;                // added to all of it; the latest of it
+    auto give = [&](int64_t c) {
+        const int64_t v = free_at[0] + c;
+        end = std::max(end, v);
+        int k = 0;
+        for (int l; (l = 2 * k + 1) < blocks; k = l) {
+            if (l + 1 < blocks && free_at[l + 1] < free_at[l]) l++;
+            if (free_at[l] >= v) break;
+            free_at[k] = free_at[l];
+        }
+        free_at[k] = v;
+    };
+    for (const auto& q : insts) {
+        const int64_t per = z.samples(q.second), c = cost(per, q.second);
+        for (int64_t k = q.first / per; k > 0;) {
+            if (k >= blocks && end - free_at[0] <= c) {  // one for each block, as often as it goes
+                base += k / blocks * c;
+                k %= blocks;
+            } else {
+                give(c);
+                k--;
+            }
+        }
+        if (q.first % per) give(cost(q.first % per, q.second));
+    }
+    return base + end;
+}
+
+// Item sizes per kind. Per-sample and direct kinds (about two blocks per CU): at
+// least eight items for a block where the batch is large enough, so that they end
+// together, at most max_pairs, and at least several times an item's overheads at
+// the kind's 9e9 points/s per block: a set of 748 items of 4x4-shape instances
+// took 69, 49 and 47 us with 30000, 100000 and 200000. With max_pairs alone (2^22)
+// an instance of 2e5 samples and M = 4 was one block's work.
+// 32 x 32 kind (a block per CU): whichever of max_pairs, its halves and the size
+// by that rule ends first by batch_span. Small items cost their overhead each,
+// large ones leave a last round part full, and where they fill rounds exactly
+// nothing is won by cutting them: max_pairs alone, the first rule alone, and so:
+//   8-D M = 512, 3 x 592404 samples     214 us   301 us   218 us
+//   8-D M = 2048, 8 x 50000             169      200      171
+//   4-D M = 1024, 8 x 134577            304      236      232
+//   8-D M = 512, 1 x 1000000            213      182      126
+//   8-D M = 2048, 1 x 100000            160       66       66
+static void item_sizes(const mdgmi_instance* inst, const std::vector<int>& kind, const std::vector<int>& order,
+                       int64_t max_pairs, ItemSize (&size)[3]) {
     int64_t total[3] = {0, 0, 0};
     for (size_t q = 0; q < kind.size(); q++) total[kind[q]] += inst[q].n * sample_cost(kind[q], inst[q].fmt->M);
     for (int k = 0; k < 3; k++) {
         const int64_t blocks = (int64_t)device_cu_count() * (k == kKindMfma ? 1 : 2);
         const int64_t least = k == kKindMfma ? 400000 : 200000;
-        cost[k] = std::max(least, std::min(max_pairs, total[k] / (8 * blocks)));
+        const int align = k == kKindMfma ? 32 * kMfmaWaves : (k == kKindSmall ? kSmallItemAlign : 64 * kDirectWaves);
+        size[k] = {std::max(least, std::min(max_pairs, total[k] / (8 * blocks))), (int)sample_cost(k, 0), align};
+    }
+    std::vector<std::pair<int64_t, int>> mfma;
+    for (int q : order)
+        if (kind[q] == kKindMfma) mfma.push_back({inst[q].n, inst[q].fmt->M});
+    const int cus = device_cu_count();
+    ItemSize z = size[kKindMfma];
+    int64_t items = 0;
+    for (const auto& q : mfma) items += (q.first + z.samples(q.second) - 1) / z.samples(q.second);
+    if (items <= cus) return;  // one round of the smallest
+    int64_t best = z.size < max_pairs ? batch_span(mfma, z, cus, INT64_MAX) : INT64_MAX;
+    z.extra = 0;
+    if (best == INT64_MAX) {  // more than eight rounds of the largest
+        size[kKindMfma] = {max_pairs, 0, z.align};
+        return;
+    }
+    for (z.size = max_pairs; z.size >= 200000; z.size /= 2) {
+        const int64_t span = batch_span(mfma, z, cus, best);
+        if (span < best) {
+            best = span;
+            size[kKindMfma] = z;
+        }
     }
 }
 
@@ -271,8 +349,8 @@ int plan_batch(const mdgmi_instance* inst, int n_inst, int path, int64_t item_pa
         return inst[a].fmt->M > inst[b].fmt->M;
     });
     P.insts.resize(n_inst);
-    int64_t item_cost[3];
-    item_costs(inst, kind, item_pairs, item_cost);
+    ItemSize item_size[3];
+    item_sizes(inst, kind, order, item_pairs, item_size);
     // items are grouped per instance in the order above; (first, end) per
     // caller instance lets the reduction find them
     std::vector<int32_t> first_of(n_inst), count_of(n_inst);
@@ -280,10 +358,7 @@ int plan_batch(const mdgmi_instance* inst, int n_inst, int path, int64_t item_pa
         const int q = order[oi];
         const mdgmi_format* f = inst[q].fmt;
         const int64_t n = inst[q].n;
-        const int align = kind[q] == kKindMfma ? 32 * kMfmaWaves
-                                               : (kind[q] == kKindSmall ? kSmallItemAlign : 64 * kDirectWaves);
-        int64_t per = item_cost[kind[q]] / sample_cost(kind[q], f->M);
-        per = std::max<int64_t>(align, per / align * align);
+        const int64_t per = item_size[kind[q]].samples(f->M);
         first_of[q] = (int32_t)P.items.size();
         for (int64_t s0 = 0; s0 < n; s0 += per) {
             BatchItem it;
