@@ -14,7 +14,9 @@ demapper (trained on exact-LLR targets, then timed against the exact path on
 the same held-out samples with per-SNR fallback), and the FP64 CPU oracle on
 a bounded sample.
 
-Prints one JSON line. `--gpus N` with N > 1 exits: the figure is one GPU's.
+Prints one JSON line: the timed workload's entries and the single figures of the
+other legs; the whole record, with every curve, goes to standard error
+(`[bench] record {...}`). `--gpus N` with N > 1 exits: the figure is one GPU's.
 """
 from __future__ import annotations
 
@@ -630,6 +632,27 @@ def ragged_leg(args, log, scale=None):
             "count_scale": scale, "unit": "sample*points/s"}
 
 
+CONTRACT = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config", "roofline")
+
+
+def short(v):
+    """v without notes and arrays of more than four (or of composite) entries,
+    floats to six digits."""
+    if isinstance(v, dict):
+        return {k: t for k, t in ((k, short(x)) for k, x in v.items() if k != "note") if t is not None}
+    if isinstance(v, list):
+        return [short(x) for x in v] if len(v) <= 4 and not any(isinstance(x, (dict, list)) for x in v) else None
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
+def result_line(record):
+    """The result line: the timed workload's entries as they are, of the other
+    legs their single figures. (The whole record, 23 KB with every curve, was cut
+    off where the line is read back.)"""
+    return json.dumps({k: v if k in CONTRACT else short(v) for k, v in record.items()})
+
+
 def main():
     args = parse()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) > 1:
@@ -774,7 +797,8 @@ def main():
         line["ragged_batch_small"] = ragged_leg(args, log, scale=args.ragged_scale * 0.01)
     if not args.no_cpu_baseline:
         line["cpu_baseline"] = cpu_baseline(wl, args.cpu_seconds)
-    print(json.dumps(line))
+    log("record " + json.dumps(line))
+    print(result_line(line), flush=True)
 
 
 if __name__ == "__main__":
