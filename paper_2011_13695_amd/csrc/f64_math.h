@@ -54,11 +54,11 @@ __device__ __forceinline__ double exp_neg(double d, const ExpScale& s) {
     return __hiloint2double(__double2hiint(v) + (n << 20), __double2loint(v));
 }
 
-// a / b for normal a, b and quotient (no range scaling): v_rcp_f64, two Newton
-// steps and a residual correction, within 1 ulp.
+// a / b for normal a, b and quotient (no range scaling): v_rcp_f64, a Newton step
+// (45 bits from its 22 or more) and Markstein's residual correction, which makes
+// up for the rest: within 0.5 ulp but for rare last bits.
 __device__ __forceinline__ double fast_div(double a, double b) {
     double r = __builtin_amdgcn_rcp(b);
-    r = fma(fma(-b, r, 1.0), r, r);
     r = fma(fma(-b, r, 1.0), r, r);
     const double q = a * r;
     return fma(fma(-b, q, a), r, q);
@@ -67,9 +67,10 @@ __device__ __forceinline__ double fast_div(double a, double b) {
 // ln x for normal positive x, within about 1 ulp: x = 2^e v, v in [sqrt(1/2),
 // sqrt(2)), f = v - 1 (exact), s = f / (2 + f), and the atanh series ln v =
 // 2 s + s R(s^2) with R its terms from 2/3 s^2 on, to s^20 (the next is below
-// 3e-17), put together as f - s (f - R) so that s needs no extra digits. A
-// third of the library log's instructions, whose two-word arithmetic has no
-// use here: the sums it is taken of carry more than its rounding.
+// 3e-17), put together as f - s (f - R) so that s needs no extra digits (that
+// regrouping, and ln 2 in two parts, as in fdlibm's logarithm). A third of the
+// library log's instructions, whose two-word arithmetic has no use here: the sums
+// it is taken of carry more than its rounding.
 __device__ __forceinline__ double ln_pos(double x) {
     double v = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
     int e = __builtin_amdgcn_frexp_exp(x);
@@ -93,14 +94,15 @@ __device__ __forceinline__ double ln1p_pos(double x) {
 }
 
 // sqrt x for x and its root well inside the normal range (no range scaling):
-// v_rsq_f64, one coupled Newton step and two residual corrections.
+// v_rsq_f64, one step of Goldschmidt's coupled iteration for root and half its
+// reciprocal (45 bits from 22 or more), and Markstein's residual correction:
+// within 0.5 ulp but for rare last bits.
 __device__ __forceinline__ double sqrt_pos(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
     const double r = fma(-h, g, 0.5);
     g = fma(g, r, g);
     h = fma(h, r, h);
-    g = fma(fma(-g, g, x), h, g);
     return fma(fma(-g, g, x), h, g);
 }
 
@@ -108,24 +110,27 @@ __device__ __forceinline__ double sqrt_pos(double x) {
 // 4): a - k fl(pi / 2) is exact in one fma, a second one takes the rest of
 // pi / 2 off, so the remainder r carries 53 bits also next to a zero. Chebyshev
 // interpolants in z = r^2 up to (pi / 4)^2 of (sin r - r) / (r z) and
-// (cos r - 1 + z / 2) / z^2, degree 5: 2e-17 and 1e-18 off, within 1 ulp in all.
+// (cos r - 1 + z / 2) / z^2, degree 5: 2e-17 and 1e-18 off (what 1 - z / 2 loses to
+// rounding goes back in with the series, as in fdlibm's cosine, and so does what r
+// itself loses, rl: 0.29 ulp root mean square and 0.8 at most (0.36 and 1.4 without
+// rl; a correctly rounded result 0.289 and 0.5).
 __device__ __forceinline__ void sincos_turn(double a, uint32_t k, double& sn, double& cs) {
     constexpr double S[6] = {-0x1.5555555555555p-3, 0x1.1111111110bb2p-7,   -0x1.a01a019e83aaep-13,
                              0x1.71de37968a024p-19, -0x1.ae600b02a7c74p-26, 0x1.5e0b19f38405ap-33};
     constexpr double C[6] = {0x1.5555555555555p-5,   -0x1.6c16c16c16967p-10, 0x1.a01a019f4eb00p-16,
                              -0x1.27e4fa17da030p-22, 0x1.1eeb68e934339p-29,  -0x1.907da36274fc5p-37};
     const double kd = (double)k;
-    const double r = fma(-kd, 0x1.1a62633145c07p-54, fma(-kd, 0x1.921fb54442d18p+0, a));
-    const double z = r * r;
+    const double r0 = fma(-kd, 0x1.921fb54442d18p+0, a);
+    const double r = fma(-kd, 0x1.1a62633145c07p-54, r0), rl = fma(-kd, 0x1.1a62633145c07p-54, r0 - r);
+    const double z = r * r, w = fma(-0.5, z, 1.0);
     double s = S[5], c = C[5];
 #pragma unroll
     for (int i = 4; i >= 0; i--) {
         s = fma(s, z, S[i]);
         c = fma(c, z, C[i]);
     }
-    s = fma(r * z, s, r);
-    const double w = fma(-0.5, z, 1.0);
-    c = w + fma(z * z, c, fma(-0.5, z, 1.0 - w));
+    s = r + fma(r * z, s, rl * w);
+    c = w + fma(z * z, c, fma(-r, rl, fma(-0.5, z, 1.0 - w)));
     const bool odd = k & 1;
     const double s1 = odd ? c : s, c1 = odd ? s : c;
     sn = __hiloint2double(__double2hiint(s1) ^ (int)((k << 30) & 0x80000000u), __double2loint(s1));
