@@ -71,13 +71,8 @@ int shape_waves(const mdgmi_format* f, const MfmaVariant& v, int mode) {
     return 12;
 }
 
-// Blocks of a launch of 32 x 32 shape var: one resident round over all CUs, the
-// blocks per CU limited by the LDS image (160 KiB per CU) and by the waves (cu_waves)
-// that fit. Counted at sixteen waves for every shape, a launch of a block per tile ran
-// in two rounds of part blocks where they do not fit: 8-D M = 2048 in the bf16 split
-// (two columns, 256 registers), 313 column tiles, LLRs 57 us, and 10 ms with
-// samples on the per-class path; now 34 us and 5.1 ms (eight tiles per block: 49 us
-// and 5.3 ms).
+// Blocks over all CUs of 32 x 32 shape var: per CU as the LDS image (160 KiB) and
+// the waves (cu_waves) allow.
 int64_t shape_blocks(const mdgmi_format* f, int split, int var, int cu_waves) {
     const MfmaVariant& v = shape_of(var);
     const size_t img = image_bytes_per_snr(f, split);
@@ -93,20 +88,23 @@ LaunchCfg shape_cfg(const mdgmi_format* f, int64_t n, int n_snr, int mode, int s
     const MfmaVariant& v = shape_of(var);
     const int64_t cols = 32 * v.ncol;
     const int64_t tiles = (n + cols - 1) / cols;
-    const int64_t round = shape_blocks(f, split, var, shape_waves(f, v, mode));
     const int snr_in_launch = snr_per_launch(n_snr);
+    // blocks whose waves all have a tile, up to sixteen waves per CU
+    const int64_t full = std::min((tiles + v.waves - 1) / v.waves, shape_blocks(f, split, var, 16) / snr_in_launch);
     // a launch of few samples takes a block per column tile as far as they fit
     // beside each other: the tiles go to the blocks in turn, a wave or two of each
     // has work, and a SIMD with one busy wave is through its tile in a third of the
     // time. By the launch's points, not the call's: 8-D M = 2048, 40 points of 700
-    // samples (two launches of 440 tiles) 98 us with sixteen tiles per block, 56 us so
-    int64_t per = std::min(round / snr_in_launch, tiles);
-    // LLR blocks do not end together in a reduction: up to sixteen waves per CU
-    // with a tile each, also where they run behind each other (2-D M = 1024, 2.5e6
-    // samples: 360 us, 378 in one round of eight waves per CU)
-    if (mode_is_llr(mode))
-        per = std::max(per, std::min((tiles + v.waves - 1) / v.waves, shape_blocks(f, split, var, 16) / snr_in_launch));
-    per = std::max<int64_t>(1, per);
+    // samples (two launches of 440 tiles) 98 us with sixteen tiles per block, 56 us
+    // so. Blocks that do not fit would be a second round of part blocks: 8-D M = 2048
+    // in the bf16 split (two columns, 256 registers), 313 column tiles, LLRs 57 us, and
+    // 10 ms with samples on the per-class path; so 34 us and 5.1 ms (eight tiles
+    // per block: 49 us and 5.3 ms).
+    const int64_t beside = shape_blocks(f, split, var, shape_waves(f, v, mode)) / snr_in_launch;
+    // Blocks whose waves all have work may run behind each other: they take the
+    // points in order, so that fewer images share an L2 (the same format, 16
+    // points of 10^6 samples: 5.6 ms, 6.2 in one round).
+    const int64_t per = std::max<int64_t>(1, std::max(full, std::min(beside, tiles)));
     LaunchCfg c;
     c.threads = v.waves * 64;
     c.blocks_per_snr = (int)per;
@@ -179,7 +177,7 @@ int64_t mfma_blocks_bound(const mdgmi_format* f, int64_t n, int n_snr, int mode,
     };
     int64_t b = 0;
     for (int v = -1; v < kNumVariants; v++)
-        b = std::max(b, bound(kMaxSnrPerLaunch, shape_blocks(f, split, v, shape_waves(f, shape_of(v), mode)), (n + 31) / 32));
+        b = std::max(b, bound(kMaxSnrPerLaunch, shape_blocks(f, split, v, 16), (n + 31) / 32));
     if (split == kSplitF16) b = std::max(b, bound(kMaxSnrPerLaunch, split_blocks(f), (n + 31) / 32));
     if (split == kSplitF16 && small_shape_fits(f))
         b = std::max(b, bound(kMaxSnrSmall, small_blocks(f, 1, mode), small_want(n)));

@@ -64,21 +64,26 @@ def test_split_points(rules):
     assert split > 1000
 
 
-def test_one_resident_round(rules):
-    """Blocks of a launch fit beside each other: of the bf16 split's two-column
-    shape (256 registers) one of eight waves per CU, of the one-column shapes of
-    eight waves two for GMI of up to four dimensions (122), else one. Launches of LLRs
-may have more, of which every wave has work."""
+def test_part_blocks_fit(rules):
+    """Blocks without work for all their waves fit beside each other: of the bf16
+    split's two-column shape (256 registers) one of eight waves per CU, of the
+    one-column shapes of eight waves two for GMI of up to four dimensions (122), else
+    one. With work for every wave, and LDS for their images, sixteen waves per CU are
+    kept in launches of any mode."""
     fs = list(forms())
     seen = 0
     for f, (blocks, threads, variant, sp) in zip(fs, rules(fs)):
         if variant == SMALL or sp:
             continue
         dim, M, s, mode, n_snr, n = f
-        waves = threads // 64
+        waves, points = threads // 64, per_launch(n_snr)
         fit = 8 if variant in WIDE else 16 if waves == 16 or (mode == 0 and dim <= 4) else 12
-        full = -(-n // (32 * (2 if variant in WIDE else 1) * waves))  # blocks whose waves all have a tile
-        beside = CUS * max(1, fit // waves) // per_launch(n_snr)
-        assert blocks <= max(1, beside, full if mode in (1, 3) else 0), (f, blocks, threads)
+        tiles = -(-n // (32 * (2 if variant in WIDE else 1)))
+        full = -(-tiles // waves)   # blocks whose waves all have a tile
+        beside = CUS * max(1, fit // waves) // points
+        assert blocks <= max(1, beside, full), (f, blocks, threads)
+        image_kib = -(-M // 32) * ((6 * dim + 21) // 16 if s else 1 + (dim == 8))
+        if image_kib <= 64 or image_kib > 128:   # two blocks' images fit, or it is read from L2
+            assert blocks >= min(full, CUS * (16 // waves) // points), (f, blocks, threads)
         seen += 1
     assert seen > 1000
