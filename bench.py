@@ -44,7 +44,7 @@ HBM_PEAK = 8.0e12
 # the same counter reads for a plain copy kernel of known size (a 1 GiB copy
 # reads FETCH_SIZE = 0.5 GiB and WRITE_SIZE = 1 GiB: factors 2.0 and 1.0).
 # Reported only while the kernel sources hash to the value they were taken on.
-TRAFFIC = {"sources_sha1": "c260537035890229a839beba98aed416feb8643d", "fetch_kib": 2821972.625, "write_kib": 1040.0,
+TRAFFIC = {"sources_sha1": "fb03fe5de1ddb6f24d18954b9408864682bd955a", "fetch_kib": 2821970.5625, "write_kib": 1040.0,
            "fetch_scale": 2.0, "write_scale": 1.0}
 KERNEL_SOURCES = ("mfma_core.h", "mfma_kernels.h", "device_common.h", "internal.h", "exact_mfma_d8_f16.hip")
 
@@ -647,10 +647,12 @@ def short(v):
 
 
 def result_line(record):
-    """The result line: the timed workload's entries as they are, of the other
-    legs their single figures. (The whole record, 23 KB with every curve, was cut
-    off where the line is read back.)"""
-    return json.dumps({k: v if k in CONTRACT else short(v) for k, v in record.items()})
+    """The result line: the timed workload's entries as they are (its GMI and MI to
+    six digits), of the other legs their single figures. (The whole record, 23 KB
+    with every curve, was cut off where the line is read back.)"""
+    line = {k: v if k in CONTRACT else short(v) for k, v in record.items()}
+    line.update({k: [float(f"{v:.6g}") for v in record[k]] for k in ("gmi", "mi") if k in record})
+    return json.dumps(line)
 
 
 def main():

@@ -21,3 +21,4 @@ def test_result_line_is_short():
     for k in bench.CONTRACT:
         assert out[k] == rec[k]
     assert out["leg0"]["a"] == {"value": 7.12346e12, "ms": 0.142857, "pair": [0.333333, 2]}
+    assert out["gmi"] == [float(f"{v:.6g}") for v in curve[:16]]
