@@ -339,7 +339,9 @@ int mdgmi_gmi_static(const mdgmi_format* fmt, const void* y, const uint32_t* tx_
  * kernel: the samples of every instance are cut into items of at most about
  * 2^22 sample*points, a persistent grid pulls items from an atomic counter and
  * dispatches each to the direct or MFMA code of its (dim, M); per-item FP64
- * partials are reduced per instance in item order (bit-reproducible). */
+ * partials are reduced per instance in item order: the same batch gives the
+ * same bits (an instance's items, and with them the last bits of its sums,
+ * follow from the whole batch). */
 typedef struct {
     const mdgmi_format* fmt;  /* staged format of this instance (any dim, M)   */
     const float* y;           /* device [n][dim] float                          */

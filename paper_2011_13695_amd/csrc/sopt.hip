@@ -14,14 +14,15 @@
 // C' (bisection, or doubling while no upper end is known), until it has
 // converged. The first kSoptAhead passes are launches of their own (k_sopt_pass),
 // each of which takes the step from the sums of the one before in its prologue;
-// the rest, seldom needed, are one launch (k_sopt_rest). Once the search has
-// ended the remaining launches return at once.
+// whatever passes are left are one launch (k_sopt_rest), after one that settles
+// the state they start from: eight launches a call. Once the search has ended the
+// remaining ones return at once.
 //
 // What bounds it: a pass over 1000003 x 11 FP32 LLRs takes 12 us (48 MB, 4.0
-// TB/s: the copy rate), the step in its prologue and the launch about 5 us;
-// five passes, 110 us a call. (The library's expf, log1pf and divisions per LLR
-// and one 4-byte load each made a pass 69 us, and the 60 pairs of launches past
-// the last needed pass 4 us each: 509 us.)
+// TB/s: the copy rate), the step in its prologue and the launch about 5 us; five
+// passes, and three launches after the end, 110 us a call. (The library's expf,
+// log1pf and divisions per LLR and one 4-byte load each made a pass 69 us, and the
+// 60 pairs of launches past the last needed pass 4 us each: 509 us.)
 #include <algorithm>
 
 #include "device_common.h"
@@ -34,7 +35,10 @@ namespace {
 constexpr int kSoptThreads = 256;
 constexpr int kSoptPart = 6;      // sum C, sum C^2, sum C', sum C'', sum v, non-finite
 constexpr int kSoptPasses = 64;
-constexpr int kSoptAhead = 6;    // matched and scaled Gaussian LLRs converge in 3-5
+// Gaussian LLRs of unequal bits scaled by 0.5 to 1.4 take 5-7 passes in FP32, 6-8 in
+// FP64 (matched ones 3-4): a seventh one, in k_sopt_rest, takes a 4-bit FP64 call of
+// 100001 samples from 55 to 73 us
+constexpr int kSoptAhead = 6;
 constexpr int kSearchThreads = 512;
 // state of the search: s, lo, hi, passes done, best GMI so far, ended, the s
 // reported so far. Two slots, written in turn; then the words that order the
